@@ -1,8 +1,10 @@
 """Benchmark: candidate plans scored per second on one MI355X.
 
-A step is one dy_plan_select over the workload's whole plan set: the seeding
-pre-pass, the fp32 scoring pass over every plan, certification of the
-candidates in fp64 and the copy of the K winners back to the host.  The
+A step is one dy_plan_select over the workload's whole plan set: seeding, the
+fp32 pass (every row scored, or every plan of a range decided: scored, or shut
+out by a bound on all plans that share its first nodes, see "per_unit" for the
+work counted), certification of the candidates in fp64 and the copy of the K
+winners back to the host.  The
 problem tables are staged once (dy_plan_create) before timing; their staging
 time is reported separately as "stage_ms".
 
@@ -75,7 +77,7 @@ CSRC = "paper_2607_02942_amd/csrc/"
 
 
 def kernel_sources(kernel):
-    own = CSRC + ("jit_rows.cpp" if kernel.startswith("dy_") else "kernels.hip")
+    own = CSRC + ("jit_rows.cpp" if kernel.startswith("dy_") else "solve.hip" if kernel == "k_solve" else "kernels.hip")
     return (own, CSRC + "dyplan_internal.h", CSRC + "host.cpp")
 
 
@@ -88,7 +90,7 @@ WORKLOADS = ["chain4", "forkjoin8", "layered10", "batch6", "stream24"]
 # ---------------------------------------------------------------------------
 
 def kernel_base(name):
-    """Base name of a (demangled) kernel name: 'void dyp::k_sweep<false, 12, 4>(...)' -> 'k_sweep'."""
+    """Base name of a (demangled) kernel name: 'void dyp::k_solve<0>(...)' -> 'k_solve'."""
     depth, out = 0, []
     for ch in name.split("(")[0]:  # drop template arguments
         if ch == "<":
@@ -157,10 +159,10 @@ def _steps(counts, hits):
     """Steps in a profiled run: every selection call certifies once (one
     k_certify dispatch for up to 65,535 sources); without it (the score
     bench) each step launches each matched kernel once.  A step may launch
-    a kernel several times: one instantiation per group of sources (k_sweep
+    a kernel several times: one instantiation per group of sources (k_solve
     with and without prefix sinks), or one launch per share of a rows source
     scored in two shares."""
-    cert = match_kernel(counts.keys(), "k_certify")
+    cert = match_kernel(counts.keys(), "k_certify") or match_kernel(counts.keys(), "k_solve")
     if cert:
         return counts[cert[0]]
     return max(counts[h] for h in hits)
@@ -317,65 +319,25 @@ def edge_count(prob):
     return len({(int(u), int(v)) for u, v in prob.edges})
 
 
-def sweep_work_per_plan(prob, ydiv=False):
-    """Algorithmic fp32 operations per plan of the prefix-shared sweep.
+def sweep_work_per_plan(prob, objective=False):
+    """Algorithmic fp32 operations per plan of the range sweep.
 
-    Per plan: 1 multiply (corr), 1 add (CP), 1 compare (prefilter); per row of
-    the inner sweep (R_y plans): the add and multiply of node x and the max of
-    y's predecessors; per block (R_x R_y plans): the prefix products and one
-    max/add per prefix edge.  Counted like the full recurrence, operation by
-    operation, so the figure never exceeds the work actually done.
-
-    ydiv: the sweep compares x's product (the rest of a plan's corr) with
-    thresholds divided ahead by each implementation of y's factor, so a plan
-    costs 1 add (CP) and 1 selection operation (the min of its CP bin's
-    threshold into its row's least threshold; the row's last one is the
-    compare with x's product) and no multiply.  The bin's address (an AND of
-    the CP's pattern) is addressing, not counted.
+    The sweep's unit is a head, one assignment of every node but the last
+    three, whose implementations are folded into tables beforehand.  Per head:
+    per node a multiply (objective: two adds) and the add of its duration, one
+    max per edge into a head node or one of the last three; then three bounds
+    (the paths into the last three), each an add, a scaling and a compare, and
+    the two products with the largest factors (objective: one add and a scaling
+    for the bin of D, a fused multiply-add and a compare per path).  The few
+    heads that pass, the seeding, the tables and the certification are not
+    counted, so the figure stays below the work actually done.
     """
     n = prob.n_nodes
-    rx = int(prob.radix[n - 2]) if n >= 2 else 1
-    ry = int(prob.radix[n - 1])
+    nh = max(n - 3, 0)
     edges = {(int(u), int(v)) for u, v in prob.edges}
-    npre = max(n - 2, 0)
-    pre_edges = sum(1 for u, v in edges if v < npre)
-    x_pred = sum(1 for u, v in edges if v == n - 2)
-    y_pred = sum(1 for u, v in edges if v == n - 1 and u != n - 2)
-    per_plan = 2.0 if ydiv else 3.0
-    per_row = 2.0 + (1.0 if (n - 2, n - 1) in edges and y_pred > 0 else 0.0)
-    per_block = max(npre - 1, 0) + pre_edges + x_pred + y_pred
-    return per_plan + per_row / ry + per_block / (rx * ry)
-
-
-def obj_sweep_work_per_plan(prob, yshift=False):
-    """Algorithmic fp32 operations per plan of the objective-mode sweep.
-
-    Per plan: the add of y's duration (T), the max with the prefix sinks' path
-    when there is one, the adds of y's utility (U) and d (D), the fused
-    multiply-add G = U - lambda_l T and the prefilter compare; per row: the
-    adds of node x (its path, utility and d) and the max of y's predecessors;
-    per block: the prefix sums of u and d and one max/add per prefix edge.
-
-    yshift: the sweep compares the row's R = ux - lambda_l M (one fused
-    multiply-add per row) with bin thresholds lowered ahead by each
-    implementation of y's utility and latency term, so a plan costs the add of
-    its D and 1 selection operation (the min of its D bin's threshold into the
-    row's least threshold; the row's last one is the compare with R).
-    """
-    n = prob.n_nodes
-    rx = int(prob.radix[n - 2]) if n >= 2 else 1
-    ry = int(prob.radix[n - 1])
-    edges = {(int(u), int(v)) for u, v in prob.edges}
-    npre = max(n - 2, 0)
-    pre_edges = sum(1 for u, v in edges if v < npre)
-    x_pred = sum(1 for u, v in edges if v == n - 2)
-    y_pred = sum(1 for u, v in edges if v == n - 1 and u != n - 2)
-    pre_sinks = any(all(u != m for u, v in edges) for m in range(npre))
-    has_s2 = pre_sinks or (n - 2, n - 1) not in edges
-    per_plan = 2.0 if yshift else 5.0 + (1.0 if has_s2 else 0.0)
-    per_row = (4.0 if yshift else 3.0) + (1.0 if (n - 2, n - 1) in edges and y_pred > 0 else 0.0)
-    per_block = 2 * max(npre - 1, 0) + pre_edges + x_pred + y_pred
-    return per_plan + per_row / ry + per_block / (rx * ry)
+    into = sum(1 for u, v in edges if u < nh)
+    head = nh * (3 if objective else 2) + into + (8 if objective else 11)
+    return head / float(np.prod([int(r) for r in prob.radix[max(n - 3, 0):]]))
 
 
 def full_work_per_plan(prob, K):
@@ -668,7 +630,7 @@ def main():
     def timed_loop(tag, collect):
         # collect: read the library's per-call statistics after every step
         # (the caller-side loop does not, as a caller needs only the choices)
-        cands, main_ms, gen, ydiv = [], [], [], []
+        cands, main_ms, gen = [], [], []
         ev0 = torch.cuda.Event(enable_timing=True)
         ev1 = torch.cuda.Event(enable_timing=True)
         torch.cuda.synchronize()
@@ -680,17 +642,16 @@ def main():
                 main_ms.append(s.main_ms)
                 cands.append(s.candidates)
                 gen.append(s.generated_jobs)
-                ydiv.append(s.ydiv_jobs)
             if i == 0 or (i + 1) % max(1, args.steps // 4) == 0:
                 print(f"[bench] {tag} step {i + 1}/{args.steps}", file=sys.stderr, flush=True)
         ev1.record(stream)
         torch.cuda.synchronize()
-        return ev0.elapsed_time(ev1) / args.steps, main_ms, cands, gen, ydiv
+        return ev0.elapsed_time(ev1) / args.steps, main_ms, cands, gen
 
     # 1) the steps as a caller runs them: repeated calls replay one HIP graph
     for _ in range(args.warmup):
         step()
-    ms_per_step, _, _, _, _ = timed_loop("step", False)
+    ms_per_step, _, _, _ = timed_loop("step", False)
     value = plans / (ms_per_step / 1e3)
     got_graph = [[out[j * plan.kmax + k].as_tuple() for k in range(K)] for j in range(len(sources))]
     # 2) the same calls with the library's HIP events around the scoring kernel
@@ -698,7 +659,7 @@ def main():
     plan.set_option(D.DY_OPT_TIMING, 1)
     for _ in range(max(1, args.warmup // 2)):
         step()
-    ms_per_step_timed, main_ms, cands, gen, ydiv = timed_loop("timed", True)
+    ms_per_step_timed, main_ms, cands, gen = timed_loop("timed", True)
     got_timed = [[out[j * plan.kmax + k].as_tuple() for k in range(K)] for j in range(len(sources))]
     generated = bool(gen) and max(gen) > 0  # the library ran a kernel generated for the problem
     kern_ms = float(np.mean(main_ms))
@@ -712,30 +673,18 @@ def main():
                 "traffic": stored_traffic(tkey, kbase), "per_unit": "24 B of row per plan", "kernel_ms": kern_ms,
                 "achieved_units_per_step": units, "peak_scale": 1e9}
     else:
-        # sources whose sweep took the pre-divided thresholds (every one or none
-        # in these workloads: one DAG, or requests of one shape)
-        yd = max(ydiv) if ydiv else 0
-        if yd not in (0, len(sources)):
-            raise RuntimeError(f"{yd} of {len(sources)} sources took the pre-divided thresholds")
-        if objs:
-            units = sum(obj_sweep_work_per_plan(probs[p], yd > 0) * c for _, p, _, c in specs)
-        else:
-            units = sum(sweep_work_per_plan(probs[p], yd > 0) * c for _, p, _, c in specs)
+        units = sum(sweep_work_per_plan(probs[p], objs is not None) * c for _, p, _, c in specs)
         f = units / plans
         achieved = units / (kern_ms / 1e3)
         if generated:
-            kbase = "dy_sweep"
-            kname = "dy_sweep (generated for the DAG" + (", objective)" if objs else ")")
-        else:
-            kbase = "k_sweep_obj" if objs else "k_sweep"
-            kname = kbase
-        roof = {"bound": "alu", "kernel": kname, "achieved": achieved / 1e12,
+            raise RuntimeError("a generated sweep ran: its work is not counted here")
+        kbase = "k_solve"
+        roof = {"bound": "alu", "kernel": kbase, "achieved": achieved / 1e12,
                 "peak": PEAK_VALU / 1e12, "unit": "TFLOP/s", "frac": achieved / PEAK_VALU,
                 "peak_packed_fp32": PEAK_VALU_PACKED / 1e12, "frac_vs_packed_fp32": achieved / PEAK_VALU_PACKED,
                 "traffic": stored_traffic(tkey, kbase),
-                "per_unit": f"{f:.4f} fp32 ops per plan (prefix-shared sweep{', objective' if objs else ''}"
-                            + ((", thresholds lowered ahead by y's terms" if objs else
-                                ", thresholds divided ahead by y's factor") if yd else "")
+                "per_unit": f"{f:.4f} fp32 ops per plan (one bound per assignment of all but the last three nodes"
+                            f"{', objective' if objs else ''}; seeding and certification run in the same kernel"
                             + (", mean over the requests' DAGs" if len(specs) > 1 else "") + ")",
                 "kernel_ms": kern_ms, "achieved_units_per_step": units, "peak_scale": 1e12}
         if not objs:

@@ -194,38 +194,38 @@ typedef struct dy_choice {
 
 /* Statistics of the last dy_plan_select call on a handle. */
 typedef struct dy_stats {
-    uint64_t plans;          /* plans scored */
+    uint64_t plans;          /* plans of the sources, each scored or decided by a bound it fails */
     uint64_t candidates;     /* plans re-evaluated in fp64 for certification */
     int32_t fallbacks;       /* (source, level) pairs decided by the exhaustive fp64 path */
     int32_t n_jobs;          /* sources in the call */
     float main_ms;           /* duration of the main scoring kernel(s), when timing is on */
     float total_ms;          /* launch of the first kernel to the end of the last */
     int32_t generated_jobs;  /* sources whose main pass ran a kernel generated for their problem */
-    int32_t ydiv_jobs;       /* sources whose sweep took its bin thresholds divided (corr) or lowered
-                                (objective) ahead by each implementation of node y: per plan one add (CP, or
-                                the demand D) and a min into the row's threshold, one compare per row */
+    int32_t ydiv_jobs;       /* RANGE sources swept on thresholds made ahead for the last nodes: by the library's
+                                sweep (thresholds folded over the last three nodes' implementations), or a
+                                generated one (divided, or lowered, by each implementation of the last) */
 } dy_stats;
 
 /* Options for dy_plan_set_option. */
 enum {
     DY_OPT_TIMING = 1,          /* 1: record HIP events around the kernels of each call (default 0) */
-    DY_OPT_SAMPLE_STRIDE = 2,   /* the seeding pre-pass scores 1 of every S work units (default 128) */
+    DY_OPT_SAMPLE_STRIDE = 2,   /* the seeding pre-pass scores 1 of every S work units (default 128; RANGE
+                                   sources seed from constructed plans instead, unless they run a
+                                   generated sweep) */
     DY_OPT_CAND_CAPACITY = 3,   /* candidate slots per source (default 1 << 16, min 16) */
     DY_OPT_FORCE_FP64 = 4,      /* 1: decide every level with the exhaustive fp64 path (default 0) */
     DY_OPT_JIT = 5,             /* kernels generated for the problem (hiprtc): 0 never; 1 (default) for
-                                   rows, per-plan scores of 32-bit RANGE sources of DAGs above 16 nodes,
-                                   and the sweep of 32-bit RANGE sources of at least 2^24 plans in
-                                   plans of at most 8 problems;
-                                   2 as 1 but the sweep for RANGE sources of any size */
+                                   rows, and per-plan scores of rows; 2 as 1 and for the sweep of 32-bit
+                                   RANGE sources in plans of at most 8 problems */
     DY_OPT_GRAPH = 6,           /* 1: replay a call that repeats the previous one (same sources) from a
                                    HIP graph of its launches (default 1; calls with DY_OPT_TIMING on
                                    launch directly); results are identical */
     DY_OPT_CLIMB = 7            /* local-search seeds: RANGE sources that cover the whole plan space of a
                                    problem of at most 8 nodes also seed each level's threshold from a
-                                   local search over the plans (the sampling pass then thins out); under
-                                   the additive objective only when lambda_l and every lambda_ld L_k are
-                                   not negative.  0: never; 1 (default): in calls of at least 128 such
-                                   sources; 2: for every such source.  Results are identical */
+                                   local search over the plans; under the additive objective only when
+                                   lambda_l and every lambda_ld L_k are not negative.  0: never; 1
+                                   (default): where they pay, at present nowhere; 2: for every such
+                                   source.  Results are identical */
 };
 
 /*

@@ -15,6 +15,9 @@ constexpr int NBINS = 64;        // lane-resident prefilter table: one bin per l
 constexpr int NBINS2 = 256;      // bins of the generated sweep's prefilter (one shift-and-mask operation)
 constexpr int NSLOT = 64;        // per-level atomic slots of the seeding pass (spreads contention)
 constexpr int CERT_WAVES = 8;    // waves per source in certification when sources are few
+constexpr int SOLVE_BINS = 256;       // bins of the range sweep's tables
+constexpr int SOLVE_BINS_OBJ = 256;   // ... under the objective, which has twice the tables
+constexpr int SOLVE_WK = 32;     // working counters of a RANGE source
 constexpr int CLIMB_ENTRIES = 512;  // local search: largest sum of a problem's radices (its tables in LDS), else none
 
 // Unsigned 32-bit division by an invariant divisor (Granlund & Montgomery,
@@ -106,6 +109,30 @@ struct ProbDev {
     // lambda_l tau_j + E (E bounds the roundings of a plan's G and of its
     // row's fma(-lambda_l, M, ux)), rounded up to fp32; see yshift_key
     float ysub[64];
+    // Folded tables of the range sweep (solve.hip): bins of 2^wsh fp32
+    // patterns, the least shift >= 8 that covers [cp_lo, cp_hi] with one bin
+    // to spare; least contribution of y, of x and y, and of w = N-3 and what
+    // follows it to the value binned (the CP's paths through them; objective
+    // mode: D); largest factors; what w feeds (bit 0: x, 1: y, 2: it is a sink)
+    int32_t wsh;
+    float dmin_y, dmin_xy, dmin_w;
+    float aw_max, ax_max;
+    uint32_t w_feeds;
+    // seeding: scale of the weight of durations against ln a (3 over the mean
+    // of the nodes' largest durations), and per node the share of a unit flow
+    // from the sources to the sinks that passes through it, split evenly at forks
+    float lam0;
+    float flow[NMAX];
+    // Per-backend pressure, per level: least fp32 CP_k, bin shift of [cplo,
+    // ghi], least contributions of y, of x and y, and of w and what follows;
+    // the levels whose durations are nowhere above this level's (bit mask)
+    float cplo[KMAX];
+    int32_t csh[KMAX];
+    float cdmin[KMAX][3];
+    uint32_t nest[KMAX];
+    // objective mode: bound on the roundings between a plan's G and the row or
+    // block value its threshold is lowered to (E_s of ysub)
+    double eshift;
 };
 
 struct Cand {
@@ -126,7 +153,7 @@ struct JobDev {
     uint64_t stride;
     uint64_t index_base;
     uint64_t blk_first, nblk; // RANGE sweep: inner-pair blocks covering the range
-    uint64_t units;           // work units of the main kernel (blocks for the sweep, plans otherwise)
+    uint64_t units;           // work units of the main kernel (heads for RANGE, plans otherwise)
     uint32_t sample_stride;
     uint32_t cap;             // candidate slots
     uint32_t* scert;          // [KMAX][NSLOT] best certainly-feasible fp32 corr found by the pre-pass, bits + 1 (0: none)
@@ -151,7 +178,16 @@ struct JobDev {
     int32_t* hflags;
     uint32_t* hdone;          // host-mapped completion word of the call (with hout), set last
     int32_t climb;            // RANGE source over its problem's whole plan space: local-search seeds
-    int32_t gblk;             // library sweep: consecutive blocks per thread (units = nblk / gblk)
+    // RANGE sources (solve.hip): units are heads, the first with index ublk0;
+    // working counters (candidates, finished workgroups), zero between
+    // launches; the source's workgroups; whether slot 0 of each level of scert
+    // holds a seed
+    uint64_t ublk0;
+    uint8_t dig0[NMAX], dig1[NMAX];  // digits of the first and last plan
+    uint32_t* wk;             // [SOLVE_WK]
+    int32_t nwg;
+    int32_t seeded;
 };
+
 
 }  // namespace dyp

@@ -21,8 +21,9 @@ hipError_t launch_init(JobDev* d_jobs, int njobs, hipStream_t s);
 hipError_t launch_table(JobDev* d_jobs, int njobs, hipStream_t s);
 hipError_t launch_sample_sweep(const JobDev* d_jobs, int n, bool has_s2, bool obj, uint64_t max_samples,
                                int npre_max, int npre_c, int kmax, hipStream_t s);
-hipError_t launch_sweep(const JobDev* d_jobs, int n, bool has_s2, bool obj, uint64_t max_units, int npre_max,
-                        int npre_c, int ry, bool b256, bool rad12, int pat, hipStream_t s);
+// (weak: a build of the host code alone links without it)
+hipError_t launch_solve(const JobDev* d_jobs, int n, int mode, int nwg, int ent, int rmax, int nmax, int lat,
+                        int col, hipStream_t s) __attribute__((weak));
 hipError_t launch_sample_generic(const JobDev* d_jobs, int n, uint64_t max_samples, int ncol, hipStream_t s);
 hipError_t launch_scan(const JobDev* d_jobs, int n, uint64_t max_units, int ncol, hipStream_t s);
 hipError_t launch_certify(const JobDev* d_jobs, int njobs, int waves, int kmax, int nmax, int nrmax, hipStream_t s);
@@ -60,7 +61,6 @@ constexpr int kDirectResults = 64;                // up to this many sources, re
 constexpr int kStaticSources = 64;                // sources per dy_plan_select_static call at most
 constexpr uint32_t kStaticMinCand = 1024;         // candidate slots per source it needs at least
 constexpr int kClimbNodes = 8;                    // local-search seeds for problems of at most this many nodes
-constexpr int kClimbMinSources = 128;             // ... in calls of at least this many such sources (DY_OPT_CLIMB 1)
 // ROWS sources of at least kSplitRows rows under per-backend pressure
 // (generated kernels) are scored in two shares: the first 1/kSplitShare of the
 // rows, then the candidates gathered so far re-seed the thresholds
@@ -70,7 +70,9 @@ constexpr int kClimbMinSources = 128;             // ... in calls of at least th
 // unless the thresholds are near the optimum; under uniform pressure the
 // sampled seeds already abandon most rows early and a second share measured
 // no gain.
-constexpr uint64_t kSweepRunMin = 1ull << 20;    // library sweep: runs of blocks per thread for groups of this many blocks
+constexpr int kSolveWgs = 4;                      // workgroups per CU that the RANGE sources of a call share
+constexpr uint64_t kSolveSteps = 4;              // units per thread, at least, of a source of several workgroups
+constexpr int kSolveUnrolled = 9;                 // prefix nodes of the range sweep's unrolled recurrences
 constexpr uint64_t kSplitRows = 1ull << 22;
 constexpr uint64_t kSplitShare = 32;
 constexpr uint64_t kSplitStride = 512;
@@ -89,6 +91,7 @@ struct Scratch {
     size_t jobs = 0;            // sources the buffers hold
     bool clean = false;         // every job slot's seeds, counters and flags are zero (no k_init needed)
     uint32_t* sync = nullptr;   // [jobs] certification block counters
+    uint32_t* wk = nullptr;     // [jobs][SOLVE_WK] counters of the RANGE sources' workgroups
     uint32_t cap = 0;           // candidate slots per source
     int kmax = 0;
     char* d = nullptr;
@@ -354,26 +357,26 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 }  // namespace
 
-// The kernel family that scores a source.
-// Sources of one call are launched in groups: the prefix-shared sweep (RANGE,
-// uniform pressure; with or without a second sink term; corr / SLO or the
-// additive objective), the generic per-plan path, and the generated rows kernels.
-enum Group { G_SWEEP = 0, G_SWEEP_S2 = 1, G_OSWEEP = 2, G_OSWEEP_S2 = 3, G_GENERIC = 4, G_JIT = 5 };
-constexpr int kGroups = 6, kSweepGroups = 4;
+// The kernel family that scores a source.  Sources of one call are launched
+// in groups: RANGE sources whose sweep is generated for their DAG (with or
+// without a second sink term; corr / SLO or the additive objective), the
+// generic per-plan path, the generated rows kernels, and the other RANGE
+// sources (one launch from seeds to choices each for uniform pressure,
+// per-backend pressure and the objective).
+enum Group { G_SWEEP = 0, G_SWEEP_S2 = 1, G_OSWEEP = 2, G_OSWEEP_S2 = 3, G_GENERIC = 4, G_JIT = 5, G_SOLVE = 6 };
+constexpr int kGroups = 9, kSweepGroups = 4, kSolveModes = 3;  // G_SOLVE + mode: 0 uniform, 1 per-backend, 2 objective
 
 struct PassPlan {
     int n[kGroups] = {};                  // sources per group, stored in group order
     uint64_t units[G_JIT] = {};           // largest main-pass work of the group
     uint64_t samples[G_JIT] = {};         // largest seeding-pass work of the group
     int npre[kSweepGroups] = {};
-    int ry[kSweepGroups] = {};            // R_y shared by every source of a sweep group, else -1
     int npre_c[kSweepGroups] = {};        // prefix length shared by every source of a sweep group, else -1
-    int pat[kSweepGroups] = {};           // largest prefix-row table (npre x rmax entries) of a sweep group
     int ydiv_jit[kSweepGroups] = {};      // generated sweeps on thresholds divided (corr) or lowered (objective) by y's terms
-    int sample_lib[kSweepGroups] = {};    // library-sweep sources the sampling pass seeds (see launch_seed)
-    int njit[kSweepGroups] = {};          // trailing sources of the group that run their generated sweep
-    bool b256[kSweepGroups] = {true, true, true, true};  // every library-sweep source has the 256-bin table
-    bool rad12[kSweepGroups] = {true, true, true, true}; // ... and 12 implementations per prefix node, 32-bit blocks
+    // RANGE sources of each mode: workgroups of the largest, largest node
+    // table, R_max and node count, most prefix nodes not unrolled
+    int nwg[kSolveModes] = {}, ent[kSolveModes] = {}, rmax[kSolveModes] = {}, nmax[kSolveModes] = {},
+        lat[kSolveModes] = {}, col[kSolveModes] = {};
     int kmax = 1;                         // most levels of any source
     int climb_e = 0;                      // largest sum of radices of a source that climbs
     int climb_n = 0;                      // most nodes of a source that climbs
@@ -499,6 +502,7 @@ size_t layout_scratch(Scratch& s, char* d, size_t njobs, uint32_t cap, int km) {
     size_t o_fbc = take(njobs * KMAX * sizeof(uint64_t));
     size_t o_fbi = take(njobs * KMAX * sizeof(uint64_t));
     size_t o_sync = take(njobs * sizeof(uint32_t));
+    size_t o_wk = take(njobs * SOLVE_WK * sizeof(uint32_t));
     size_t o_cand = take(njobs * (size_t)cap * sizeof(Cand));
     off = align_up(off, 256);
     s.res_bytes = res_bytes;
@@ -524,6 +528,7 @@ size_t layout_scratch(Scratch& s, char* d, size_t njobs, uint32_t cap, int km) {
     s.ncand = (uint32_t*)(d + o_res + res_ncand);
     s.flags = (int32_t*)(d + o_res + res_flags);
     s.sync = (uint32_t*)(d + o_sync);
+    s.wk = (uint32_t*)(d + o_wk);
     s.fb_corr = (uint64_t*)(d + o_fbc);
     s.fb_index = (uint64_t*)(d + o_fbi);
     s.cand = (Cand*)(d + o_cand);
@@ -679,6 +684,7 @@ void stage_objective(const dy_problem& pb, ProbDev& D, float2* at, float2* atx, 
     // by the 2^-50 margin before rounding up.
     const double A0 = (su + D.lam_l64 * tmax) * grow;
     const double Es = 4.0 * kU * A0 * (1.0 + 0x1p-10) + (4.0 + 4.0 * D.lam_l64) * 0x1p-149;
+    D.eshift = Es;
     const int ry = std::min(pb.radix[N - 1], 64);
     for (int i = 0; i < 64; ++i) {
         float c = 0.0f;
@@ -944,6 +950,73 @@ int stage_problems(dy_plan* h, const dy_problem* probs, int32_t n_probs, std::st
             D.ay_max = std::max(D.ay_max, v.x);
             D.ty_min = std::min(D.ty_min, v.y);
         }
+        // folded tables of the range sweep: bins, least contributions of x and y
+        const uint32_t nb = obj ? SOLVE_BINS_OBJ : SOLVE_BINS;
+        D.wsh = 8;
+        while (D.wsh < 31 && ((D.cp_hi_bits >> D.wsh) - (D.cp_lo_bits >> D.wsh)) > nb - 2) ++D.wsh;
+        auto least = [&](int n, bool d) {
+            float m = INFINITY;
+            for (int i = 0; i < pb.radix[n]; ++i)
+                m = std::min(m, d ? dem[(size_t)n * R + i] : at[(size_t)n * R + i].y);
+            return m;
+        };
+        auto most = [&](int n) {  // (a missing node's factor is 1)
+            float m = n >= 0 ? 0.0f : 1.0f;
+            for (int i = 0; n >= 0 && i < pb.radix[n]; ++i) m = std::max(m, at[(size_t)n * R + i].x);
+            return m;
+        };
+        const float mw = N >= 3 ? least(N - 3, obj) : 0.0f, mx = N >= 2 ? least(N - 2, obj) : 0.0f;
+        D.ax_max = most(N - 2);
+        D.aw_max = most(N - 3);
+        if (N >= 3)
+            D.w_feeds = (D.pred[N - 2] >> (N - 3) & 1u) | (D.pred[N - 1] >> (N - 3) & 1u) << 1 |
+                        (D.sinks >> (N - 3) & 1u) << 2;
+        {
+            double sum = 0.0;
+            int roots = 0;
+            for (int n = 0; n < N; ++n) {
+                float m = 0.0f;
+                for (int i = 0; i < pb.radix[n]; ++i) m = std::max(m, at[(size_t)n * R + i].y);
+                sum += (double)m;
+                roots += D.pred[n] == 0;
+            }
+            D.lam0 = sum > 0.0 ? (float)std::min(3.0 * N / sum, 1e30) : 0.0f;
+            int out[DY_MAX_NODES] = {};
+            for (int n = 0; n < N; ++n)
+                for (int u = 0; u < n; ++u) out[u] += D.pred[n] >> u & 1u;
+            for (int n = 0; n < N; ++n) {
+                double x = D.pred[n] == 0 ? 1.0 / roots : 0.0;
+                for (int u = 0; u < n; ++u)
+                    if (D.pred[n] >> u & 1u) x += (double)D.flow[u] / out[u];
+                D.flow[n] = (float)x;
+            }
+        }
+        for (int k = 0; k < K && !obj && !uniform; ++k) {
+            const float* lk = lat + (size_t)k * N * R;
+            float dmin[DY_MAX_NODES];
+            for (int n = 0; n < N; ++n) {
+                dmin[n] = INFINITY;
+                for (int i = 0; i < pb.radix[n]; ++i) dmin[n] = std::min(dmin[n], lk[(size_t)n * R + i]);
+            }
+            D.cplo[k] = cp32(N, D.pred, D.sinks, dmin);
+            const uint32_t top = f2u(std::max(D.ghi, D.cplo[k])), bot = f2u(D.cplo[k]);
+            D.csh[k] = 8;
+            while (D.csh[k] < 30 && (top >> D.csh[k]) - (bot >> D.csh[k]) > nb - 3) ++D.csh[k];
+            const float cw = N >= 3 ? dmin[N - 3] : 0.0f, cx = N >= 2 ? dmin[N - 2] : 0.0f;
+            D.cdmin[k][0] = dmin[N - 1];
+            D.cdmin[k][1] = D.edge_xy ? cx + dmin[N - 1] : cx;
+            D.cdmin[k][2] = cw + (D.w_feeds & 1u ? D.cdmin[k][1] : D.w_feeds & 2u ? D.cdmin[k][0] : 0.0f);
+            for (int j = 0; j < k; ++j) {
+                const float* lj = lat + (size_t)j * N * R;
+                bool below = true;
+                for (int n = 0; n < N && below; ++n)
+                    for (int i = 0; i < pb.radix[n]; ++i) below = below && lj[(size_t)n * R + i] <= lk[(size_t)n * R + i];
+                if (below) D.nest[k] |= 1u << j;
+            }
+        }
+        D.dmin_y = least(N - 1, obj);
+        D.dmin_xy = obj || D.edge_xy ? mx + D.dmin_y : mx;
+        D.dmin_w = mw + (obj || D.w_feeds & 1u ? D.dmin_xy : D.w_feeds & 2u ? D.dmin_y : 0.0f);
         {
             const int ry = std::min(pb.radix[N - 1], 64);
             const float2* ay = (const float2*)(img.data() + L.at) + (size_t)(N - 1) * R;
@@ -1030,7 +1103,6 @@ JobDev make_job(const dy_plan* h, const dy_source& s) {
     J.stride = s.row_stride;
     J.index_base = s.index_base;
     J.sample_stride = h->sample_stride;
-    J.gblk = 1;
     if (s.kind == DY_SOURCE_RANGE) {
         const uint64_t inner = (uint64_t)H.rx * (uint64_t)H.ry;
         J.blk_first = s.begin / inner;
@@ -1308,33 +1380,25 @@ hipError_t launch_jit_seed(const dy_plan* h, const JobDev& J, int p, hipStream_t
     return hipModuleLaunchKernel(h->jit[p].seed, gx, 1, 1, 256, 1, 1, 0, s, args, nullptr);
 }
 
-// Seeding pre-pass of the sweep and generic groups (jobs stored in group order at d; host copies at
-// hjobs).  Jobs of the generated sweep whose problem has a generated seeding pass take it.
+// Seeding pre-pass of the generated sweeps and the generic group (jobs stored
+// in group order at d; host copies at hjobs).  A problem without a generated
+// seeding pass takes the library's.
 void launch_seed(const dy_plan* h, const JobDev* d, const JobDev* hjobs, const PassPlan& pp, hipStream_t s,
                  const std::function<void(hipError_t, const char*)>& chk) {
-    auto chunks = [&](const JobDev* base, int n, auto&& fn) {
-        for (int c = 0; c < n; c += 65535) fn(base + c, std::min(65535, n - c));
-    };
-    for (int g = 0; g < kSweepGroups; ++g) {
-        const int lib = pp.n[g] - pp.njit[g];
-        auto lib_launch = [&](const JobDev* b, int n) {
-            chk(launch_sample_sweep(b, n, (g & 1) != 0, g >= G_OSWEEP, pp.samples[g], pp.npre[g], pp.npre_c[g],
-                                    pp.kmax, s),
-                "sample");
-        };
-        if (pp.sample_lib[g] > 0) chunks(d + pp.before(g), lib, lib_launch);
-        for (int q = pp.before(g) + lib; q < pp.before(g) + pp.n[g]; ++q) {
+    for (int g = 0; g < kSweepGroups; ++g)
+        for (int q = pp.before(g); q < pp.before(g) + pp.n[g]; ++q) {
             const int p = (int)(hjobs[q].prob - h->d_probs);
             if (h->jit[p].seed)
                 chk(launch_jit_seed(h, hjobs[q], p, s), "generated seeding");
             else
-                lib_launch(d + q, 1);
+                chk(launch_sample_sweep(d + q, 1, (g & 1) != 0, g >= G_OSWEEP, pp.samples[g], pp.npre[g],
+                                        pp.npre_c[g], pp.kmax, s),
+                    "sample");
         }
-    }
-    chunks(d + pp.before(G_GENERIC), pp.n[G_GENERIC],
-           [&](const JobDev* b, int n) {
-               chk(launch_sample_generic(b, n, pp.samples[G_GENERIC], pp.ncol, s), "sample");
-           });
+    for (int c = 0; c < pp.n[G_GENERIC]; c += 65535)
+        chk(launch_sample_generic(d + pp.before(G_GENERIC) + c, std::min(65535, pp.n[G_GENERIC] - c),
+                                  pp.samples[G_GENERIC], pp.ncol, s),
+            "sample");
 }
 
 void launch_table_all(const JobDev* d, int ntot, hipStream_t s,
@@ -1343,7 +1407,6 @@ void launch_table_all(const JobDev* d, int ntot, hipStream_t s,
         chk(launch_table(const_cast<JobDev*>(d + c), std::min(65535, ntot - c), s), "table");
 }
 
-// Scoring pass of the sweep and generic groups.
 // The generated sweep of one RANGE source (host copy J of its job).
 hipError_t launch_jit_sweep(const dy_plan* h, const JobDev& J, int p, hipStream_t s) {
     const ProbDev& D = h->hdesc[p];
@@ -1385,25 +1448,50 @@ hipError_t launch_jit_sweep(const dy_plan* h, const JobDev& J, int p, hipStream_
     return hipSuccess;
 }
 
-// Main scoring pass.  hjobs: host copies of the jobs at d (for the sources of
-// the sweep groups that run their generated sweep, the last pp.njit[g] of the
-// group); null when pp.njit is all zero.
+// Main scoring pass of the generated sweeps, the generic group and the RANGE
+// sources that one launch takes from seeds to choices.
 void launch_main(const dy_plan* h, const JobDev* d, const JobDev* hjobs, const PassPlan& pp, hipStream_t s,
                  const std::function<void(hipError_t, const char*)>& chk) {
-    auto chunks = [&](const JobDev* base, int n, auto&& fn) {
-        for (int c = 0; c < n; c += 65535) fn(base + c, std::min(65535, n - c));
-    };
-    for (int g = 0; g < kSweepGroups; ++g) {
-        chunks(d + pp.before(g), pp.n[g] - pp.njit[g], [&](const JobDev* b, int n) {
-            chk(launch_sweep(b, n, (g & 1) != 0, g >= G_OSWEEP, pp.units[g], pp.npre[g], pp.npre_c[g], pp.ry[g],
-                             pp.b256[g], pp.rad12[g], pp.pat[g], s),
-                "sweep");
-        });
-        for (int q = pp.before(g) + pp.n[g] - pp.njit[g]; q < pp.before(g) + pp.n[g]; ++q)
+    for (int g = 0; g < kSweepGroups; ++g)
+        for (int q = pp.before(g); q < pp.before(g) + pp.n[g]; ++q)
             chk(launch_jit_sweep(h, hjobs[q], (int)(hjobs[q].prob - h->d_probs), s), "generated sweep");
+    for (int c = 0; c < pp.n[G_GENERIC]; c += 65535)
+        chk(launch_scan(d + pp.before(G_GENERIC) + c, std::min(65535, pp.n[G_GENERIC] - c), pp.units[G_GENERIC],
+                        pp.ncol, s),
+            "scan");
+    for (int m = 0; m < kSolveModes; ++m)
+        for (int c = 0; c < pp.n[G_SOLVE + m]; c += 65535)
+            chk(launch_solve(d + pp.before(G_SOLVE + m) + c, std::min(65535, pp.n[G_SOLVE + m] - c), m, pp.nwg[m],
+                             pp.ent[m], pp.rmax[m], pp.nmax[m], pp.lat[m], pp.col[m], s),
+                "solve");
+}
+
+// The launch bounds of RANGE source J (mode m) of a plan.
+void add_solve(PassPlan& pp, int m, const JobDev& J, const ProbDev& D) {
+    pp.nwg[m] = std::max(pp.nwg[m], J.nwg);
+    pp.ent[m] = std::max(pp.ent[m], D.n * D.rmax);
+    pp.rmax[m] = std::max(pp.rmax[m], D.rmax);
+    pp.nmax[m] = std::max(pp.nmax[m], D.n);
+    if (m == 1) pp.lat[m] = std::max(pp.lat[m], D.k * D.n * D.rmax);
+    if (m == 1 || D.npre > kSolveUnrolled) pp.col[m] = std::max(pp.col[m], m == 1 ? D.n : D.npre);
+}
+
+// How RANGE source J is split: `share` workgroups of the device are its part
+// of the call (by its blocks); a workgroup takes several units per thread, so
+// that the first of them (a seeding step) pays.
+void split_source(JobDev& J, const ProbDev& D, uint64_t share) {
+    const uint64_t rw = D.npre > 0 ? (uint64_t)D.radix[D.npre - 1] : 1;
+    J.ublk0 = J.blk_first / rw;
+    J.units = (J.blk_first + J.nblk - 1) / rw - J.ublk0 + 1;
+    uint64_t p0 = J.begin, p1 = J.begin + J.count - 1;
+    for (int n = D.n - 1; n >= 0; --n) {
+        const uint64_t r = (uint64_t)D.radix[n];
+        J.dig0[n] = (uint8_t)(p0 % r);
+        J.dig1[n] = (uint8_t)(p1 % r);
+        p0 /= r;
+        p1 /= r;
     }
-    chunks(d + pp.before(G_GENERIC), pp.n[G_GENERIC],
-           [&](const JobDev* b, int n) { chk(launch_scan(b, n, pp.units[G_GENERIC], pp.ncol, s), "scan"); });
+    J.nwg = (int32_t)std::min<uint64_t>(std::max<uint64_t>(share, 1), (J.units + WG * kSolveSteps - 1) / (WG * kSolveSteps));
 }
 
 void launch_certify_all(const JobDev* d, int ntot, int cert_waves, const dy_plan* h, hipStream_t s,
@@ -1442,6 +1530,9 @@ bool jit_ready(dy_plan* h, int p) {
 }
 
 }  // namespace
+
+// The group of a RANGE source of problem H.
+static int solve_group(const HostProb& H) { return G_SOLVE + (H.obj ? 2 : H.uniform ? 0 : 1); }
 
 // First share of a ROWS job scored in two shares (0: one pass).
 static uint64_t split_rows(const JobDev& J, const ProbDev& D) {
@@ -1508,47 +1599,47 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
             const int p = src[j].problem;
             const HostProb& H = h->hp[p];
             if (src[j].kind == DY_SOURCE_RANGE)
-                grp[j] = H.obj ? (H.has_s2 ? G_OSWEEP_S2 : G_OSWEEP) : (H.has_s2 ? G_SWEEP_S2 : G_SWEEP);
+                grp[j] = solve_group(H);
             else if (src[j].kind == DY_SOURCE_ROWS && !h->force_fp64 && jit_use(p))
                 grp[j] = G_JIT;
             else
                 grp[j] = G_GENERIC;
         }
-        // RANGE sources of 32-bit plan indices run the sweep generated for their DAG, when the plan has few
-        // problems (one compilation each), the source is large enough to repay
-        // it (2^24 plans; every source with DY_OPT_JIT 2) and it compiles; they
-        // go last in their group, whose library sweep launch covers the others
-        std::vector<char> jsw(n_src, 0);
-        const uint64_t jit_min = h->use_jit >= 2 ? 1 : (1ull << 24);
-        if (h->use_jit && !h->force_fp64 && h->hp.size() <= 8)
+        // DY_OPT_JIT 2: RANGE sources of 32-bit plan indices run the sweep
+        // generated for their DAG, when the plan has few problems (one
+        // compilation each) and it compiles
+        if (h->use_jit >= 2 && !h->force_fp64 && h->hp.size() <= 8)
             for (int j = 0; j < n_src; ++j) {
                 const int p = src[j].problem;
-                if (src[j].kind == DY_SOURCE_RANGE && src[j].count >= jit_min &&
-                    src[j].begin + src[j].count - 1 <= 0xffffffffull && jit_use(p) && h->jit[p].sweep)
-                    jsw[j] = 1;
+                const HostProb& H = h->hp[p];
+                if (src[j].kind == DY_SOURCE_RANGE && src[j].begin + src[j].count - 1 <= 0xffffffffull && jit_use(p) &&
+                    h->jit[p].sweep)
+                    grp[j] = H.obj ? (H.has_s2 ? G_OSWEEP_S2 : G_OSWEEP) : (H.has_s2 ? G_SWEEP_S2 : G_SWEEP);
             }
-        // local-search seeds (whole-space RANGE sources of problems of at most
-        // kClimbNodes nodes, either objective): in calls of many such sources, where they replace
-        // most of the sampling and of the certification work; a call of a few
-        // sources waits for the searches' latency instead (tens of microseconds)
+        // local-search seeds (DY_OPT_CLIMB 2: whole-space RANGE sources of
+        // problems of at most kClimbNodes nodes, either objective).  The plans
+        // that the range sweep constructs for itself are as good where it
+        // matters, at a tenth of the time: on 4,096 six-node requests the
+        // search took 97 of a step's microseconds to leave 14 candidates a
+        // source where the constructed plans leave 25.
         auto climb_ok = [&](int j) {
             const HostProb& H = h->hp[src[j].problem];
             return !h->force_fp64 && H.n <= kClimbNodes && src[j].kind == DY_SOURCE_RANGE &&
                    src[j].begin == 0 && !H.plans_saturated && src[j].count == H.n_plans;
         };
-        int n_climb = 0;
-        for (int j = 0; j < n_src; ++j) n_climb += climb_ok(j) ? 1 : 0;
-        const bool climb = h->use_climb == 2 || (h->use_climb == 1 && n_climb >= kClimbMinSources);
+        const bool climb = h->use_climb == 2;
         order.clear();
         order.reserve(n_src);
         for (int g = 0; g < kGroups; ++g)
-            for (int pass = 0; pass < 2; ++pass)
-                for (int j = 0; j < n_src; ++j)
-                    if (grp[j] == g && jsw[j] == pass) order.push_back(j);
+            for (int j = 0; j < n_src; ++j)
+                if (grp[j] == g) order.push_back(j);
         C.plans = 0;
         C.all_units = 0;
         pp = PassPlan();
         jobs.resize((size_t)n_src);
+        double all_blocks = 0.0;  // of the RANGE sources, which share the device by them
+        for (int j = 0; j < n_src; ++j)
+            if (src[j].kind == DY_SOURCE_RANGE) all_blocks += (double)make_job(h, src[j]).nblk;
         for (int q = 0; q < n_src; ++q) {
             const int j = order[q];
             const int g = grp[j];
@@ -1577,8 +1668,10 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
             J.cert_cp = S.cert_cp + (size_t)q * KMAX * CERT_WAVES;
             J.cert_d = S.cert_d + (size_t)q * KMAX * CERT_WAVES;
             J.sync = S.sync + q;
+            J.wk = S.wk + (size_t)q * SOLVE_WK;
             J.fb_levels = h->force_fp64 ? (H.k == 32 ? 0xffffffffu : ((1u << H.k) - 1u)) : 0u;
             J.climb = climb && climb_ok(j) ? 1 : 0;
+            J.seeded = J.climb;
             int climb_entries = 0;  // the search's table entries (it runs when they fit CLIMB_ENTRIES)
             if (J.climb) {
                 for (int n = 0; n < H.n; ++n) climb_entries += h->hdesc[src[j].problem].radix[n];
@@ -1586,7 +1679,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
                 pp.climb_n = std::max(pp.climb_n, H.n);
             }
             // seeding work units: rows of the inner sweep, or plans
-            const bool sweep = g < kSweepGroups;
+            const bool sweep = src[j].kind == DY_SOURCE_RANGE;
             const uint64_t sunits = sweep ? J.nblk * (uint64_t)H.rx : J.count;
             uint64_t stride = h->sample_stride;
             if (!h->stride_fixed) stride = std::max<uint64_t>(1, std::min<uint64_t>(stride, sunits / kMinSamples));
@@ -1596,74 +1689,31 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
             if (!h->stride_fixed && g == G_JIT && split_rows(J, h->hdesc[src[j].problem]))
                 stride = std::max<uint64_t>(stride, std::min<uint64_t>(kSplitStride, sunits / kMinSamples));
             J.sample_stride = (uint32_t)stride;
-            J.units = sweep ? J.nblk : J.count;
+            J.units = J.count;
             ++pp.n[g];
-            if (g < kSweepGroups && jsw[j]) ++pp.njit[g];
-            if (g < kSweepGroups && jsw[j] && h->hdesc[src[j].problem].jsh != 0 && H.ry >= 1 && H.ry <= 64)
+            if (sweep) {
+                const ProbDev& Dp = h->hdesc[src[j].problem];
+                split_source(J, Dp, (uint64_t)((double)J.nblk / all_blocks * (double)(kSolveWgs * h->cus)));
+                if (g >= G_SOLVE) add_solve(pp, g - G_SOLVE, J, Dp);
+            }
+            if (g < kSweepGroups && h->hdesc[src[j].problem].jsh != 0 && H.ry >= 1 && H.ry <= 64)
                 ++pp.ydiv_jit[g];
             if (g < G_JIT) {
                 pp.units[g] = std::max(pp.units[g], J.units);
                 pp.samples[g] = std::max(pp.samples[g], (sunits + stride - 1) / stride);
             }
-            // a source of more than 2^21 plans whose levels are seeded by the
-            // local search needs no sample in corr / SLO mode under uniform
-            // pressure (the search starts from the plan of least CP, so a
-            // level it cannot seed has no certainly feasible plan at all) and
-            // in objective mode (every plan is admissible, so every level's
-            // search seeds it); on so large a space a sample of about 256 rows
-            // rarely beats the search's seed (on smaller spaces, and under
-            // per-backend pressure, it does now and then)
-            const bool climb_only = J.climb && (H.obj || H.uniform) && climb_entries <= CLIMB_ENTRIES &&
-                                    J.count > (1ull << 21);
-            if (g < kSweepGroups && !jsw[j] && !climb_only) ++pp.sample_lib[g];
             pp.kmax = std::max(pp.kmax, H.k);
             if (g == G_GENERIC) pp.ncol = std::max(pp.ncol, H.n);
-            if (sweep) {
-                if (!jsw[j] && h->hdesc[src[j].problem].jsh != 18) pp.b256[g] = false;
-                if (!jsw[j]) {
-                    const ProbDev& Dp = h->hdesc[src[j].problem];
-                    bool r12 = J.big == 0;
-                    for (int n = 0; n < Dp.npre; ++n) r12 = r12 && Dp.radix[n] == 12;
-                    if (!r12) pp.rad12[g] = false;
-                }
+            if (g < kSweepGroups) {
                 pp.npre[g] = std::max(pp.npre[g], H.npre);
-                pp.pat[g] = std::max(pp.pat[g], H.npre * H.rmax);
-                pp.ry[g] = pp.n[g] == 1 ? H.ry : (pp.ry[g] == H.ry ? pp.ry[g] : -1);
                 pp.npre_c[g] = pp.n[g] == 1 ? H.npre : (pp.npre_c[g] == H.npre ? pp.npre_c[g] : -1);
             }
             C.all_units = std::max(C.all_units, J.count);
             C.plans += J.count;
             jobs[q] = J;
         }
-        C.n3 = pp.before(G_JIT);  // jobs of the other groups; JIT jobs follow
+        C.n3 = pp.before(G_JIT);  // the rows kernels' jobs follow, then those of the solve groups
         const int n3 = C.n3;
-        // library sweep (both objectives) with a compile-time prefix length: a
-        // source whose blocks are aligned runs of G (G dividing the last prefix
-        // node's radix, up to 12) gives each thread G blocks that share the
-        // prefix but its last node; only in groups of many blocks, so that the
-        // fewer threads still fill the device (batch6's 85 M blocks: sweep 1.61
-        // -> 1.53 ms with runs of 12, 1.59 with runs of 4)
-        for (int g = 0; g < kSweepGroups; ++g) {
-            const int npc = pp.npre_c[g];
-            if (npc != 2 && npc != 4 && npc != 6 && npc != 8) continue;
-            const int q0 = pp.before(g), q1 = pp.before(g) + pp.n[g] - pp.njit[g];
-            uint64_t total = 0;
-            for (int q = q0; q < q1; ++q) total += jobs[q].nblk;
-            if (total < kSweepRunMin) continue;
-            uint64_t units = 0;
-            for (int q = q0; q < q1; ++q) {
-                JobDev& J = jobs[q];
-                const int last = h->hdesc[(int)(J.prob - h->d_probs)].radix[npc - 1];
-                for (int G : {12, 6, 4, 3, 2})
-                    if (last % G == 0 && J.blk_first % (uint64_t)G == 0 && J.nblk % (uint64_t)G == 0) {
-                        J.gblk = G;
-                        J.units = J.nblk / (uint64_t)G;
-                        break;
-                    }
-                units = std::max(units, J.units);
-            }
-            pp.units[g] = units;
-        }
         // whether any source is scored in two shares, or climbs
         C.any_split = false;
         for (int q = n3; q < n3 + pp.n[G_JIT]; ++q) C.any_split = C.any_split || split_at(jobs[q]) != 0;
@@ -1672,7 +1722,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         // every corr / SLO source that climbs is under uniform pressure (its
         // levels can share one search)
         C.climb_modes = 4;
-        for (int q = 0; q < n3; ++q)
+        for (int q = 0; q < n_src; ++q)
             if (jobs[q].climb) {
                 const ProbDev& Dq = h->hdesc[(int)(jobs[q].prob - h->d_probs)];
                 C.any_climb = true;
@@ -1687,6 +1737,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         C.valid = !stat;
     }
     const int n3 = C.n3;
+    const int n_pass = pp.before(G_SOLVE);  // jobs whose tables and certification are launches of their own
     const uint64_t plans = C.plans, all_units = C.all_units;
     const bool any_split = C.any_split, any_climb = C.any_climb;
     const int climb_modes = C.climb_modes;
@@ -1727,12 +1778,12 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
     auto issue_pre = [&](hipStream_t st, const Check& ck) {
         launch_seed(h, S.d_jobs, jobs.data(), pp, st, ck);
         if (any_climb)
-            for (int c = 0; c < n3; c += 65535)
-                ck(launch_climb(S.d_jobs + c, std::min(65535, n3 - c), pp.kmax, climb_modes, pp.climb_e, pp.climb_n,
+            for (int c = 0; c < n_src; c += 65535)
+                ck(launch_climb(S.d_jobs + c, std::min(65535, n_src - c), pp.kmax, climb_modes, pp.climb_e, pp.climb_n,
                                 st),
                    "climb");
         jit_pass(jobs.data(), n3, pp.n[G_JIT], true, st, ck);
-        launch_table_all(S.d_jobs, n_src, st, ck);
+        launch_table_all(S.d_jobs, n_pass, st, ck);
     };
     auto issue_mid = [&](hipStream_t st, const Check& ck) {
         if (h->timing) ck(hipEventRecord(h->ev[1], st), "hipEventRecord");
@@ -1750,7 +1801,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         if (h->timing) ck(hipEventRecord(h->ev[2], st), "hipEventRecord");
     };
     auto issue_post = [&](hipStream_t st, const Check& ck) {
-        launch_certify_all(S.d_jobs, n_src, cert_waves, h, st, ck);
+        launch_certify_all(S.d_jobs, n_pass, cert_waves, h, st, ck);
         if (h->timing) ck(hipEventRecord(h->ev[3], st), "hipEventRecord");
         if (n_src > kDirectResults || stat)
             ck(hipMemcpyAsync(S.h_res, S.out, S.res_bytes, hipMemcpyDeviceToHost, st), "copy out");
@@ -1833,11 +1884,11 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
     stats.plans = plans;
     stats.n_jobs = n_src;
     stats.generated_jobs = pp.n[G_JIT];
-    for (int g = 0; g < kSweepGroups; ++g) stats.generated_jobs += pp.njit[g];
-    // the library sweep takes the thresholds divided (corr) or lowered
-    // (objective) ahead by y's terms for groups on 256 bins with R_y = 12
-    for (int g : {(int)G_SWEEP, (int)G_SWEEP_S2, (int)G_OSWEEP, (int)G_OSWEEP_S2})
-        stats.ydiv_jobs += pp.ydiv_jit[g] + (pp.b256[g] && pp.ry[g] == 12 ? pp.n[g] - pp.njit[g] : 0);
+    for (int g = 0; g < kSweepGroups; ++g) {
+        stats.generated_jobs += pp.n[g];
+        stats.ydiv_jobs += pp.ydiv_jit[g];
+    }
+    for (int m = 0; m < kSolveModes; ++m) stats.ydiv_jobs += pp.n[G_SOLVE + m];
     if (h->timing) {
         float ms = 0.0f;
         if (hipEventElapsedTime(&ms, h->ev[1], h->ev[2]) == hipSuccess) stats.main_ms = ms;
@@ -1866,20 +1917,15 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
             for (int q = 0; q < n_src; ++q) {
                 if (!(S.h_flags[q] & JF_OVERFLOW)) continue;
                 const int j = order[q];
-                if (grp[j] != g) continue;
                 const HostProb& H = h->hp[src[j].problem];
+                // a generated sweep's source is rescored by the library
+                if ((grp[j] < kSweepGroups ? solve_group(H) : grp[j]) != g) continue;
                 JobDev J = jobs[q];
-                if (g < kSweepGroups) {  // the rescoring sweep takes one block per thread
-                    J.gblk = 1;
-                    J.units = J.nblk;
-                }
                 if (round < kReseedRounds) {
+                    J.seeded = 1;
                     ++rp.n[g];
                     if (g < G_JIT) rp.units[g] = std::max(rp.units[g], J.units);
-                    if (g < kSweepGroups) rp.npre[g] = std::max(rp.npre[g], H.npre);
-                    if (g < kSweepGroups) rp.pat[g] = std::max(rp.pat[g], H.npre * H.rmax);
-                    if (g < kSweepGroups && h->hdesc[src[j].problem].jsh != 18) rp.b256[g] = false;
-                    rp.rad12[g] = false;  // reseeded sources take the general kernel
+                    if (g >= G_SOLVE) add_solve(rp, g - G_SOLVE, J, h->hdesc[src[j].problem]);
                     if (g == G_GENERIC) rp.ncol = std::max(rp.ncol, H.n);
                     re.push_back(J);
                 } else {
@@ -1898,10 +1944,10 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         if (n_re > 0) {  // every overflowing source is rescored
             for (int c = 0; c < n_re; c += 65535)
                 chk(launch_reseed(S.d_fb + c, std::min(65535, n_re - c), s), "reseed");
-            launch_table_all(S.d_fb, n_re, s, chk);
-            launch_main(h, S.d_fb, nullptr, rp, s, chk);
+            launch_table_all(S.d_fb, rp.before(G_SOLVE), s, chk);
+            launch_main(h, S.d_fb, re.data(), rp, s, chk);
             jit_pass(re.data(), rp.before(G_JIT), rp.n[G_JIT], false, s, chk);
-            launch_certify_all(S.d_fb, n_re, cert_waves, h, s, chk);
+            launch_certify_all(S.d_fb, rp.before(G_SOLVE), cert_waves, h, s, chk);
         }
         if (n_ex > 0) {
             exhausted = true;

@@ -21,14 +21,17 @@
 // G >= T_k + m_k D with m_k = lambda_ld L_k >= 0, so a bin's threshold is the
 // smallest T_k + m_k D_low over the levels).
 //
-// Pipeline of one selection call (all on the caller's stream):
+// RANGE sources take one launch from seeds to choices (solve.hip).  Pipeline
+// of the other sources (and of RANGE sources with a generated sweep), all on
+// the caller's stream:
 //   k_init        zero the per-source scratch
 //   k_sample_*    seeding pre-pass: 1 in S work units, per level the best fp32
 //                 corr among plans whose fp32 CP is certainly feasible
 //   k_table       per level candidate threshold T_k (fp64 error bound on the
 //                 seed) and a 64-bin prefilter table indexed by the fp32 CP
-//   k_sweep / k_scan   the scoring pass: every plan is scored in fp32; a plan
-//                 goes to the candidate list when it could be a level's winner
+//   k_scan, generated kernels   the scoring pass: every plan is scored in fp32;
+//                 a plan goes to the candidate list when it could be a level's
+//                 winner
 //   k_certify     fp64 re-evaluation of the candidates; exact winner per level
 //                 (the last block of a source merges its waves)
 //   k_exhaust*    fallback: exhaustive fp64 decision (candidate overflow)
@@ -38,256 +41,9 @@
 
 #include <mutex>
 
-#include "dyplan_internal.h"
+#include "device_common.h"
 
 namespace dyp {
-
-// Descriptors and tables never change while a kernel runs: reading them
-// through the constant address space lets wave-uniform reads become scalar
-// loads (and the inner-sweep trip counts stay uniform).
-#if defined(__HIP_DEVICE_COMPILE__)
-#define CS __attribute__((address_space(4)))
-#else
-#define CS
-#endif
-typedef const CS ProbDev* PD;
-typedef const CS JobDev* JD;
-
-template <class T>
-__device__ __forceinline__ const CS T* cs(const T* p) {
-    return (const CS T*)p;
-}
-
-// ---------------------------------------------------------------------------
-// helpers
-// ---------------------------------------------------------------------------
-
-__device__ __forceinline__ uint32_t mdiv(uint32_t x, const CS Magic& g) {
-    uint32_t t = __umulhi(g.m, x);
-    return (t + ((x - t) >> g.sh1)) >> g.sh2;
-}
-
-// Wave-wide max of an unsigned key with DPP row shifts and row broadcasts
-// (lane 63 ends with the maximum); the result is read back uniformly.
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));  // row_shr:1
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));  // row_shr:2
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x113, 0xf, 0xf, false));  // row_shr:3
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xe, false));  // row_shr:4
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xc, false));  // row_shr:8
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-// Candidate threshold from the fp32 corr `s` of a certainly-feasible plan.
-// With |corr32 - corr64| <= g corr64 + eta for every plan (g = (2N+1) 2^-24,
-// eta = N 2^-148), the exact winner W satisfies corr32_W >= returned value.
-__device__ __forceinline__ float cand_threshold(float s, int n) {
-    if (!(s >= 0.0f)) return -INFINITY;
-    const double g = (2.0 * n + 1.0) * 0x1p-24;
-    const double eta = (double)n * 0x1p-148;
-    double t = ((double)s - eta) * (1.0 - g) / (1.0 + g) - eta;
-    t = t - fabs(t) * 0x1p-48;
-    return __double2float_rd(t);
-}
-
-// ---- objective mode: keys and thresholds ----------------------------------------
-
-// Order-preserving unsigned key of a float (a greater number has a greater
-// key; no number maps to 0, which marks "none").
-__device__ __forceinline__ uint32_t fkey(float x) {
-    const uint32_t b = __float_as_uint(x);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-
-__device__ __forceinline__ float fkey_value(uint32_t k) {
-    return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
-}
-
-__device__ __forceinline__ uint64_t dkey(double x) {
-    const uint64_t b = (uint64_t)__double_as_longlong(x);
-    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-}
-
-// An fp32 value <= a - b (exact real difference): the fp64 difference, lowered
-// by more than its rounding error, rounded down.
-__device__ __forceinline__ float sub_rd(double a, double b) {
-    double x = a - b;
-    x = x - (fabs(a) + fabs(b)) * 0x1p-50;
-    return __double2float_rd(x);
-}
-
-// Candidate threshold of level k from the best estimate s of any plan's J_k:
-// every estimate is within err2/2 of the plan's fp64 J_k, so the winner's
-// estimate is >= s - err2.
-__device__ __forceinline__ float obj_threshold(float s, double err2) {
-    return sub_rd((double)s, err2);
-}
-
-// Prefilter bin threshold: an fp32 value <= thr + m D_low (exact), m >= 0.
-__device__ __forceinline__ float obj_bin_threshold(float thr, double m, float dlow) {
-    if (thr == -INFINITY) return -INFINITY;
-    const double md = m * (double)dlow;
-    double x = (double)thr + md;
-    x = x - (fabs((double)thr) + md) * 0x1p-50;
-    return __double2float_rd(x);
-}
-
-// exact test of the scoring passes: some level's J_k estimate G - m_k D (one
-// rounding) reaches its threshold
-__device__ __forceinline__ bool is_candidate_obj(PD P, JD J, float G, float D) {
-    for (int k = 0; k < P->k; ++k)
-        if (fma(-P->m64[k], (double)D, (double)G) >= (double)J->thr[k]) return true;
-    return false;
-}
-
-// J_k = U - lambda_l T - m_k D in fp64, operation by operation as the definition
-// writes it (no contraction into fused multiply-adds).
-__device__ __forceinline__ double obj_j(double lam_l, double m, double U, double T, double D) {
-#pragma clang fp contract(off)
-    double j = lam_l * T;
-    j = U - j;
-    const double q = m * D;
-    return j - q;
-}
-
-// ---- fp64 re-evaluation ------------------------------------------------------
-// The per-node terms (1 - w(1-p), tau/(1-rho), tau*size) are precomputed on the
-// host in fp64 with the same operations as the definition, so the products,
-// sums and maxima below reproduce an fp64 evaluation of the definition in
-// node order bit for bit.  ids / f are strided per-thread columns.
-
-__device__ double ex_corr(PD P, const uint8_t* ids, int is) {
-    const CS double* a = cs(P->a64);
-    double c = 1.0;
-    for (int n = 0; n < P->n; ++n) c = c * a[n * P->rmax + ids[n * is]];
-    return c;
-}
-
-__device__ double ex_cp(PD P, const uint8_t* ids, int is, int k, double* f, int fs) {
-    const CS double* lat = cs(P->lat64) + (size_t)k * P->n * P->rmax;
-    double cp = 0.0;
-    for (int n = 0; n < P->n; ++n) {
-        double m = 0.0;
-        uint32_t pm = P->pred[n];
-        while (pm) {
-            const int u = __builtin_ctz(pm);
-            pm &= pm - 1;
-            const double fu = f[u * fs];
-            if (fu > m) m = fu;
-        }
-        const double fn = lat[n * P->rmax + ids[n * is]] + m;
-        f[n * fs] = fn;
-        if ((P->sinks >> n & 1u) && fn > cp) cp = fn;
-    }
-    return cp;
-}
-
-// Objective mode: U (returned), T and D in fp64, node order (the definition's).
-__device__ double ex_obj(PD P, const uint8_t* ids, int is, double* f, int fs, double& T, double& D) {
-    const CS double* u64 = cs(P->a64);
-    const CS double* d64 = cs(P->dem64);
-    const CS double* t64 = cs(P->lat64);
-    double U = 0.0, d = 0.0, t = 0.0;
-    for (int n = 0; n < P->n; ++n) {
-        const int e = n * P->rmax + ids[n * is];
-        if (P->llm >> n & 1u) {
-            U = U + u64[e];
-            d = d + d64[e];
-        }
-        double m = 0.0;
-        uint32_t pm = P->pred[n];
-        while (pm) {
-            const int u = __builtin_ctz(pm);
-            pm &= pm - 1;
-            const double fu = f[u * fs];
-            if (fu > m) m = fu;
-        }
-        const double fn = t64[e] + m;
-        f[n * fs] = fn;
-        if ((P->sinks >> n & 1u) && fn > t) t = fn;
-    }
-    T = t;
-    D = d;
-    return U;
-}
-
-__device__ double ex_demand(PD P, const uint8_t* ids, int is) {
-    const CS double* d64 = cs(P->dem64);
-    double d = 0.0;
-    for (int n = 0; n < P->n; ++n) d = d + d64[n * P->rmax + ids[n * is]];
-    return d;
-}
-
-// Implementation ids of plan `index` of the problem (node N-1 least significant).
-__device__ void decode64(PD P, uint64_t index, uint8_t* ids, int is) {
-    if (index <= 0xffffffffull) {
-        uint32_t x = (uint32_t)index;
-        for (int n = P->n - 1; n >= 0; --n) {
-            const uint32_t q = mdiv(x, P->rmag[n]);
-            ids[n * is] = (uint8_t)(x - q * (uint32_t)P->radix[n]);
-            x = q;
-        }
-        return;
-    }
-    for (int n = P->n - 1; n >= 0; --n) {
-        const uint64_t r = (uint64_t)P->radix[n];
-        ids[n * is] = (uint8_t)(index % r);
-        index /= r;
-    }
-}
-
-// ids of a candidate or of a fallback unit; returns false for a bad row id
-__device__ bool job_ids(JD J, PD P, uint64_t index, uint8_t* ids, int is) {
-    if (J->kind == DY_SOURCE_RANGE) {
-        decode64(P, index, ids, is);
-        return true;
-    }
-    const uint8_t* row = J->rows + (index - J->index_base) * J->stride;
-    const int N = P->n;
-    bool ok = true;
-    // eight byte loads in flight at a time (a lane otherwise waits on each)
-    for (int n0 = 0; n0 < N; n0 += 8) {
-        uint8_t v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = n0 + j < N ? row[n0 + j] : (uint8_t)0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int n = n0 + j;
-            if (n < N) {
-                uint8_t x = v[j];
-                if (x >= (uint32_t)P->radix[n]) {
-                    ok = false;
-                    x = 0;
-                }
-                ids[n * is] = x;
-            }
-        }
-    }
-    return ok;
-}
-
-__device__ __forceinline__ void append_cand(JD J, uint64_t index, float c, float cp) {
-    uint32_t slot = atomicAdd(J->ncand, 1u);
-    if (slot < J->cap) {
-        Cand* d = J->cand + slot;
-        d->index = index;
-        d->corr = c;
-        d->cp = cp;
-    } else {
-        atomicOr(J->flags, (int32_t)JF_OVERFLOW);
-    }
-}
-
-// exact per-level candidate test of the scoring pass (levels in P->k)
-__device__ __forceinline__ bool is_candidate(PD P, JD J,
-                                             float cp, float c) {
-    for (int k = 0; k < P->k; ++k)
-        if (cp <= P->hi[k] && c >= J->thr[k]) return true;
-    return false;
-}
-
 // ---------------------------------------------------------------------------
 // scratch initialisation
 // ---------------------------------------------------------------------------
@@ -317,6 +73,7 @@ __global__ void k_init(JobDev* __restrict__ jobs, int njobs) {
         *J->flags = 0;
         *J->sync = 0u;
     }
+    if (t < SOLVE_WK) J->wk[t] = 0u;
 }
 
 // True in the block of a job that finishes a launch last (once every block of
@@ -438,14 +195,6 @@ __device__ __forceinline__ const float2* stage_prefix_rows(PD P, float2* s_pat, 
     return fit ? s_pat : nullptr;
 }
 
-// Digit of prefix node n in block index b (node 0 most significant).
-__device__ __forceinline__ uint32_t prefix_digit(PD P, int n, uint64_t b, int big) {
-    if (!big) {
-        const uint32_t q = P->pv_big[n] ? 0u : mdiv((uint32_t)b, P->pvmag[n]);
-        return q - mdiv(q, P->rmag[n]) * (uint32_t)P->radix[n];
-    }
-    return (uint32_t)((b / P->pv64[n]) % (uint64_t)P->radix[n]);
-}
 
 // Prefix recurrence of block b.  NPRE > 0: the prefix has exactly NPRE nodes
 // (checked by the host); the loops unroll, every descriptor load is issued up
@@ -548,473 +297,6 @@ __device__ __forceinline__ Prefix prefix_eval(PD P, uint64_t b, int big, float* 
         }
     }
     return Prefix{pc, px, py, s, pd};
-}
-
-// Prefix of a run of blocks b0 .. b0 + G - 1 that differ only in the last
-// prefix node's digit (b0 a multiple of G, G dividing that node's radix, so
-// the digits never carry): the nodes before the last are evaluated once by
-// prefix_head, the last one per block by prefix_tail.  Same operations in
-// the same order as prefix_eval, so the same values: the product takes the
-// last node's factor last, and the maxima are exact.
-struct PrefixHead {
-    float pc;      // product of the factors of nodes 0 .. NPRE-2 (objective mode: sum of u)
-    float pd;      // objective mode: sum of d over nodes 0 .. NPRE-2
-    float m;       // the last node's predecessor maximum
-    float px, py, s;  // the maxima into x, into y and over the prefix sinks, nodes 0 .. NPRE-2
-    uint32_t d;    // the last node's digit in b0
-};
-
-template <int NPRE, bool OBJ, int RAD>
-__device__ __forceinline__ PrefixHead prefix_head(PD P, uint64_t b0, int big, const float2* s_pat, const float* s_pd) {
-    static_assert(NPRE > 1, "a head and a last node");
-    const int rmax = P->rmax;
-    float f[NPRE - 1];
-    float pc = OBJ ? 0.0f : 1.0f, pd = 0.0f;
-    uint32_t dg[NPRE];
-    if constexpr (RAD > 0) {
-        uint32_t x = (uint32_t)b0;
-#pragma unroll
-        for (int n = NPRE - 1; n >= 0; --n) {
-            dg[n] = x % (uint32_t)RAD;
-            x /= (uint32_t)RAD;
-        }
-    } else {
-#pragma unroll
-        for (int n = 0; n < NPRE; ++n) dg[n] = prefix_digit(P, n, b0, big);
-    }
-#pragma unroll
-    for (int n = 0; n < NPRE - 1; ++n) {
-        const float2 v = s_pat ? s_pat[n * rmax + dg[n]] : cs(P->at)[n * rmax + dg[n]];
-        if (OBJ) {
-            pc = pc + v.x;
-            pd = pd + (s_pat ? s_pd[n * rmax + dg[n]] : cs(P->dem)[n * rmax + dg[n]]);
-        } else {
-            pc = pc * v.x;
-        }
-        float m = 0.0f;
-        const uint32_t pm = P->pred[n];
-#pragma unroll
-        for (int u = 0; u < n; ++u)
-            if (pm >> u & 1u) m = fmaxf(m, f[u]);
-        f[n] = v.y + m;
-    }
-    float m = 0.0f, px = 0.0f, py = 0.0f, s = 0.0f;
-    const uint32_t pml = P->pred[NPRE - 1];
-    const int xn = P->xnode;
-    const uint32_t pmx = xn >= 0 ? P->pred[xn] : 0u;
-    const uint32_t pmy = P->pred[P->ynode] & (xn >= 0 ? ~(1u << xn) : ~0u);
-    const uint32_t pms = P->pre_sinks;
-#pragma unroll
-    for (int u = 0; u < NPRE - 1; ++u) {
-        if (pml >> u & 1u) m = fmaxf(m, f[u]);
-        if (pmx >> u & 1u) px = fmaxf(px, f[u]);
-        if (pmy >> u & 1u) py = fmaxf(py, f[u]);
-        if (pms >> u & 1u) s = fmaxf(s, f[u]);
-    }
-    return PrefixHead{pc, pd, m, px, py, s, dg[NPRE - 1]};
-}
-
-template <int NPRE, bool OBJ>
-__device__ __forceinline__ Prefix prefix_tail(PD P, const PrefixHead& h, int g, const float2* s_pat,
-                                              const float* s_pd) {
-    constexpr int n = NPRE - 1;
-    const int e = n * P->rmax + (int)(h.d + (uint32_t)g);
-    const float2 v = s_pat ? s_pat[e] : cs(P->at)[e];
-    const float fl = v.y + h.m;
-    const int xn = P->xnode;
-    const bool inx = xn >= 0 && (P->pred[xn] >> n & 1u);
-    const bool iny = (P->pred[P->ynode] >> n & 1u) && n != xn;
-    const bool ins = P->pre_sinks >> n & 1u;
-    const float pc = OBJ ? h.pc + v.x : h.pc * v.x;
-    const float pd = OBJ ? h.pd + (s_pat ? s_pd[e] : cs(P->dem)[e]) : 0.0f;
-    return Prefix{pc, inx ? fmaxf(h.px, fl) : h.px, iny ? fmaxf(h.py, fl) : h.py, ins ? fmaxf(h.s, fl) : h.s, pd};
-}
-
-// One plan of the inner sweep: corr = cx * a_y, CP = max(tau_y + M, S2); the
-// prefilter threshold of CP's bin is read from the 64-entry LDS table (a
-// random LDS read issues in about half the time of a lane permute on gfx950):
-// byte offset = ((bits(CP) >> bin_shift) & 63) * 4, two shift/and operations.
-// B256: the 256-bin table on shift 18 instead, whose byte offset
-// (bits(CP) >> 16) & 0x3fc is one AND of the pattern's upper half-word.
-template <bool HAS_S2, bool B256 = false>
-__device__ __forceinline__ uint64_t sweep_test(const float2 vy, float M, float S2, float cx, uint32_t sh,
-                                               const float* s_bins) {
-    float cp = vy.y + M;
-    if (HAS_S2) cp = fmaxf(cp, S2);
-    const float cc = cx * vy.x;
-    const uint32_t off = B256 ? (__float_as_uint(cp) >> 16) & 0x3fcu : (__float_as_uint(cp) >> sh) & 0xfcu;
-    const float thr = *(const float*)((const char*)s_bins + off);
-    return __ballot(cc >= thr);
-}
-
-// Threshold on the rest of the product for implementation j of y (r_j =
-// P->yinv[j]): whenever fp32(c a_j) >= T, c >= the value returned.  For T >
-// 2^-60, fp32(c a_j) >= T gives c a_j >= T / (1 + 2^-24) (both normal), and
-// fp32(T r_j) <= T r_j (1 + 2^-24) <= T / (a_j (1 + 2^-24)) since r_j <= 1 /
-// (a_j (1 + 2^-22)); smaller T, and r_j = 0 (a_j < 2^-20), give 0, which
-// every c >= 0 meets; T = +inf (no level in the bin) stays +inf.
-__device__ __forceinline__ float ydiv_threshold(float T, float r) {
-    if (T == INFINITY) return T;
-    return T > 0x1p-60f ? T * r : 0.0f;
-}
-
-// One plan of the inner sweep with the thresholds of y's implementation
-// pre-divided (s_t: its 256 bins): CP = max(tau_y + M, S2) picks the bin, whose
-// threshold on cx (the rest of the product) is returned as its fp32 pattern.
-// Every such threshold is +0, positive or +inf, so the patterns order as the
-// values do: the row's test is cx >= the least of its plans' thresholds (no
-// per-plan product or compare).  A plan that the product test admits is
-// admitted here; the rare path scores the admitted rows exactly.
-template <bool HAS_S2>
-__device__ __forceinline__ uint32_t sweep_thr_ydiv(float ty, float M, float S2, const float* s_t) {
-    float cp = ty + M;
-    if (HAS_S2) cp = fmaxf(cp, S2);
-    const uint32_t off = (__float_as_uint(cp) >> 16) & 0x3fcu;
-    return *(const uint32_t*)((const char*)s_t + off);
-}
-
-// Per-backend pressure (not uniform): the level-k state of a row of the
-// sweep, for the exact per-level tests of the seeding pass and of the rare
-// path.  `dg` holds the prefix digits of the block.  NPRE > 0: the prefix has
-// exactly NPRE nodes, the recurrence is unrolled with every f_n in a register;
-// NPRE == 0: any length, f_n in the thread's LDS column s_f.  Returns M (the
-// path into y other than through y's own duration) and S2 (the longest path
-// ending at another sink), as the sweep forms them at level 0.
-template <int NPRE>
-__device__ void level_row(PD P, const CS float* lat, const uint32_t* dg, uint64_t b, int big, int ix,
-                          float* __restrict__ s_f, float& M, float& S2) {
-    const int R = P->rmax, xn = P->xnode;
-    const uint32_t pmx = xn >= 0 ? P->pred[xn] : 0u;
-    const uint32_t pmy = P->pred[P->ynode] & (xn >= 0 ? ~(1u << xn) : ~0u);
-    float px = 0.0f, py = 0.0f, s = 0.0f;
-    if constexpr (NPRE > 0) {
-        float f[NPRE];
-#pragma unroll
-        for (int n = 0; n < NPRE; ++n) {
-            float m = 0.0f;
-            const uint32_t pm = P->pred[n];
-#pragma unroll
-            for (int u = 0; u < n; ++u)
-                if (pm >> u & 1u) m = fmaxf(m, f[u]);
-            f[n] = lat[n * R + dg[n]] + m;
-        }
-#pragma unroll
-        for (int u = 0; u < NPRE; ++u) {
-            if (pmx >> u & 1u) px = fmaxf(px, f[u]);
-            if (pmy >> u & 1u) py = fmaxf(py, f[u]);
-            if (P->pre_sinks >> u & 1u) s = fmaxf(s, f[u]);
-        }
-    } else {
-        const int tid = threadIdx.x;
-        for (int n = 0; n < P->npre; ++n) {
-            const uint32_t d = prefix_digit(P, n, b, big);
-            float m = 0.0f;
-            uint32_t pm = P->pred[n];
-            while (pm) {
-                const int u = __builtin_ctz(pm);
-                pm &= pm - 1;
-                m = fmaxf(m, s_f[u * WG + tid]);
-            }
-            s_f[n * WG + tid] = lat[n * R + d] + m;
-        }
-        auto pmax = [&](uint32_t pm) {
-            float v = 0.0f;
-            while (pm) {
-                const int u = __builtin_ctz(pm);
-                pm &= pm - 1;
-                v = fmaxf(v, s_f[u * WG + tid]);
-            }
-            return v;
-        };
-        px = pmax(pmx);
-        py = pmax(pmy);
-        s = pmax(P->pre_sinks);
-    }
-    const float fx = (xn >= 0 ? lat[xn * R + ix] : 0.0f) + px;
-    const bool exy = P->edge_xy != 0;
-    M = exy ? fmaxf(py, fx) : py;
-    S2 = exy ? s : fmaxf(s, fx);
-}
-
-template <int NPRE>
-__device__ __forceinline__ void prefix_digits(PD P, uint64_t b, int big, uint32_t* dg) {
-    if constexpr (NPRE > 0) {
-#pragma unroll
-        for (int n = 0; n < NPRE; ++n) dg[n] = prefix_digit(P, n, b, big);
-    }
-}
-
-// Rare path of the sweep under per-backend pressure: every plan of this
-// lane's row that some level admits exactly in fp32 (CP_k <= ghi and corr >=
-// T_k) goes to the candidate list once (with its unpressured CP, the value the
-// bands of the list refer to).  A level is skipped when no plan of the row
-// can reach its threshold (cx times the largest factor of y) or its band on
-// the unpressured CP (the row's smallest unpressured CP).  R_y > 64 may list
-// a plan once per level.
-template <bool HAS_S2, int NPRE>
-__device__ void general_row(PD P, JD J, uint64_t b, int big, int ix, float cx, float M0, float S20,
-                            float* __restrict__ s_f) {
-    const int N = P->n, R = P->rmax, ry = P->ry;
-    const uint64_t base = (b * (uint64_t)P->rx + (uint64_t)ix) * (uint64_t)ry;
-    const CS float2* aty = cs(P->aty);
-    uint32_t dg[NPRE > 0 ? NPRE : 1];
-    prefix_digits<NPRE>(P, b, big, dg);
-    const float cmax = cx * P->ay_max;
-    float cp0_lb = P->ty_min + M0;
-    if (HAS_S2) cp0_lb = fmaxf(cp0_lb, S20);
-    uint64_t done = 0;
-    for (int k = 0; k < P->k; ++k) {
-        const float thr = J->thr[k];
-        if (!(cmax >= thr && cp0_lb <= P->hi[k])) continue;
-        const CS float* lat = cs(P->lat) + (size_t)k * N * R;
-        float M, S2;
-        level_row<NPRE>(P, lat, dg, b, big, ix, s_f, M, S2);
-        const CS float* laty = lat + P->ynode * R;
-        if (P->lymin[k] + M > P->ghi || (HAS_S2 && S2 > P->ghi)) continue;  // every CP_k of the row above
-        if (ry <= 64) {
-            // y by decreasing factor: corr falls along the loop, which stops
-            // at the first plan below the level's threshold
-            for (int jj = 0; jj < ry; ++jj) {
-                const int iy = P->yord[jj];
-                const float2 vy = aty[iy];
-                const float cc = cx * vy.x;
-                if (!(cc >= thr)) break;
-                if (done >> iy & 1ull) continue;
-                float cp = laty[iy] + M;
-                if (HAS_S2) cp = fmaxf(cp, S2);
-                const uint64_t idx = base + (uint64_t)iy;
-                if (cp <= P->ghi && idx - J->begin < J->count) {
-                    float cp0 = vy.y + M0;
-                    if (HAS_S2) cp0 = fmaxf(cp0, S20);
-                    append_cand(J, idx, cc, cp0);
-                    done |= 1ull << iy;
-                }
-            }
-            continue;
-        }
-        for (int iy = 0; iy < ry; ++iy) {
-            if (ry <= 64 && (done >> iy & 1ull)) continue;
-            float cp = laty[iy] + M;
-            if (HAS_S2) cp = fmaxf(cp, S2);
-            const float2 vy = aty[iy];
-            const float cc = cx * vy.x;
-            const uint64_t idx = base + (uint64_t)iy;
-            if (cp <= P->ghi && cc >= thr && idx - J->begin < J->count) {
-                float cp0 = vy.y + M0;
-                if (HAS_S2) cp0 = fmaxf(cp0, S20);
-                append_cand(J, idx, cc, cp0);
-                if (ry <= 64) done |= 1ull << iy;
-            }
-        }
-    }
-}
-
-// RY > 0: every source of the launch has R_y = RY; the y table is loaded once
-// per workgroup into scalar registers and the y loop is fully unrolled, so the
-// inner sweep issues no memory load and no wait other than its LDS bin reads.
-// B256: every source of the launch has the 256-bin table (P->jsh = 18); with
-// RY > 0 the table is held per implementation of y, pre-divided by its factor
-// (s_bins[j][256], sweep_test_ydiv).
-// RAD > 0: every prefix node of every source has RAD implementations and the
-// block indices fit 32 bits (constant-divisor digits).
-// The inner sweep of block b (the prefix pf evaluated): every (x, y) pair,
-// the prefilter per plan, the exact test in the rare path.
-// Rare path of the sweep: a lane whose row (x = ix) of block b passed the
-// prefilter (mine) re-scores it with the exact test.
-template <bool HAS_S2, int NPRE>
-__device__ __forceinline__ void sweep_rare(PD P, JD J, uint64_t b, bool live, int ix, float cx, float M, float S2,
-                                           bool mine, float* s_f) {
-    if (!(live && mine)) return;
-    if (!P->uniform) {
-        general_row<HAS_S2, NPRE>(P, J, b, J->big, ix, cx, M, S2, s_f);
-        return;
-    }
-    const CS float2* aty = cs(P->aty);
-    const int ry = P->ry;
-    const uint64_t base = (b * (uint64_t)P->rx + (uint64_t)ix) * (uint64_t)ry;
-    for (int iy = 0; iy < ry; ++iy) {
-        const float2 vy = aty[iy];
-        float cp = vy.y + M;
-        if (HAS_S2) cp = fmaxf(cp, S2);
-        const float cc = cx * vy.x;
-        const uint64_t idx = base + (uint64_t)iy;
-        if (idx - J->begin < J->count && is_candidate(P, J, cp, cc)) append_cand(J, idx, cc, cp);
-    }
-}
-
-// A row of the sweep that passed the prefilter, parked in its wave's LDS
-// queue until the queue fills (or the wave's work ends), when every lane of
-// the wave re-scores one parked row: the exact test then runs on the whole
-// wave at once instead of stalling it for a single lane.
-struct RareRow {
-    uint64_t b;      // block
-    uint32_t ix;     // implementation of x
-    float cx, M, S2;
-};
-constexpr int RQ = 64;  // parked rows per wave
-
-template <bool HAS_S2, int NPRE>
-__device__ __forceinline__ void flush_rare(PD P, JD J, const RareRow* q, uint32_t n, float* s_f) {
-    const uint32_t lane = threadIdx.x & 63;
-    if (lane < n) {
-        const RareRow e = q[lane];
-        sweep_rare<HAS_S2, NPRE>(P, J, e.b, true, (int)e.ix, e.cx, e.M, e.S2, true, s_f);
-    }
-}
-
-// The row's least pre-divided threshold (see sweep_thr_ydiv).
-template <bool HAS_S2, int RY>
-__device__ __forceinline__ uint32_t sweep_row_ydiv(const float2 (&vyr)[RY], float M, float S2, const float* s_bins) {
-    uint32_t m = sweep_thr_ydiv<HAS_S2>(vyr[0].y, M, S2, s_bins);
-#pragma unroll
-    for (int j = 1; j < RY; ++j) m = min(m, sweep_thr_ydiv<HAS_S2>(vyr[j].y, M, S2, s_bins + j * NBINS2));
-    return m;
-}
-
-// q, qn, live_mask: the wave's queue of parked rows (B256 with RY > 0 only;
-// qn is wave-uniform) and the ballot of its live lanes.
-template <bool HAS_S2, int RY, int NPRE, bool B256>
-__device__ __forceinline__ void sweep_block(PD P, JD J, uint64_t b, bool live, const Prefix& pf,
-                                            const float2 (&vyr)[RY > 0 ? RY : 1], const float* s_bins,
-                                            float* s_f, RareRow* q, uint32_t& qn, uint64_t live_mask) {
-    const uint32_t sh = (uint32_t)P->bin_shift - 2u;
-    const CS float2* atx = cs(P->atx);
-    const CS float2* aty = cs(P->aty);
-    const int rx = P->rx, ry = P->ry;
-    // without a second sink x is no sink, so it feeds y
-    const bool exy = !HAS_S2 || P->edge_xy != 0;
-    if constexpr (B256 && RY > 0) {
-        for (int ix = 0; ix < rx; ++ix) {
-            const float2 vx = atx[ix];
-            const float fx = vx.y + pf.px;
-            const float cx = pf.pc * vx.x;
-            const float M = exy ? fmaxf(pf.py, fx) : pf.py;
-            const float S2 = exy ? pf.s : fmaxf(pf.s, fx);
-            const uint64_t hit =
-                __ballot(cx >= __uint_as_float(sweep_row_ydiv<HAS_S2, RY>(vyr, M, S2, s_bins))) & live_mask;
-            if (hit) {
-                const uint32_t nh = (uint32_t)__popcll(hit);
-                if (qn + nh > (uint32_t)RQ) {
-                    flush_rare<HAS_S2, NPRE>(P, J, q, qn, s_f);
-                    qn = 0;
-                }
-                const uint32_t lane = threadIdx.x & 63;
-                if (hit >> lane & 1ull) {
-                    const uint32_t o = qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32),
-                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0u));
-                    q[o] = RareRow{b, (uint32_t)ix, cx, M, S2};
-                }
-                qn += nh;
-            }
-        }
-        return;
-    }
-    for (int ix = 0; ix < rx; ++ix) {
-        const float2 vx = atx[ix];
-        const float fx = vx.y + pf.px;
-        const float cx = pf.pc * vx.x;
-        const float M = exy ? fmaxf(pf.py, fx) : pf.py;
-        const float S2 = exy ? pf.s : fmaxf(pf.s, fx);
-        uint64_t hit = 0;
-        int iy = 0;
-        if (RY > 0) {
-#pragma unroll
-            for (int j = 0; j < (RY > 0 ? RY : 1); ++j) hit |= sweep_test<HAS_S2, B256>(vyr[j], M, S2, cx, sh, s_bins);
-            iy = ry;
-        }
-        for (; iy + 4 <= ry; iy += 4) {
-            const float2 v0 = aty[iy], v1 = aty[iy + 1], v2 = aty[iy + 2], v3 = aty[iy + 3];
-            hit |= sweep_test<HAS_S2, B256>(v0, M, S2, cx, sh, s_bins);
-            hit |= sweep_test<HAS_S2, B256>(v1, M, S2, cx, sh, s_bins);
-            hit |= sweep_test<HAS_S2, B256>(v2, M, S2, cx, sh, s_bins);
-            hit |= sweep_test<HAS_S2, B256>(v3, M, S2, cx, sh, s_bins);
-        }
-        for (; iy < ry; ++iy) hit |= sweep_test<HAS_S2, B256>(aty[iy], M, S2, cx, sh, s_bins);
-        if (hit) sweep_rare<HAS_S2, NPRE>(P, J, b, live, ix, cx, M, S2, (hit >> (threadIdx.x & 63)) & 1ull, s_f);
-    }
-}
-
-// Work unit = J->gblk consecutive blocks per thread (J->units of them per
-// source): with a compile-time prefix length (NPRE > 0) the host may give a
-// source whose blocks are aligned runs of G (G dividing the last prefix
-// node's radix) G blocks per thread, which share the prefix but its last node
-// (prefix_head once, prefix_tail per block); NPRE == 0 takes one block per
-// thread.
-template <bool HAS_S2, int RY, int NPRE, bool B256, int RAD>
-__global__ void __launch_bounds__(WG) k_sweep(const JobDev* __restrict__ jobs, uint64_t unit_off, int pat_cap) {
-    extern __shared__ float s_f[];
-    JD J = cs(jobs + blockIdx.y);
-    PD P = cs(J->prob);
-    const uint64_t units = J->units;
-    const int G = NPRE > 0 ? J->gblk : 1;
-    const uint64_t t0 = unit_off + (uint64_t)blockIdx.x * WG;
-    if (t0 >= units) return;
-    const uint64_t t = t0 + threadIdx.x;
-    const bool live = t < units;
-    const uint64_t b0 = J->blk_first + (live ? t : units - 1) * (uint64_t)G;
-    constexpr bool YDIV = B256 && RY > 0;
-    __shared__ float s_bins[YDIV ? (RY > 0 ? RY : 1) * NBINS2 : (B256 ? NBINS2 : NBINS)];
-    if (B256) {
-        static_assert(!B256 || NBINS2 == WG, "one bin per thread");
-        const float thr = __uint_as_float(J->table2[threadIdx.x]);
-        if constexpr (YDIV) {
-#pragma unroll
-            for (int j = 0; j < (RY > 0 ? RY : 1); ++j)
-                s_bins[j * NBINS2 + threadIdx.x] = ydiv_threshold(thr, P->yinv[j]);
-        } else {
-            s_bins[threadIdx.x] = thr;
-        }
-    } else if (threadIdx.x < NBINS) {
-        s_bins[threadIdx.x] = __uint_as_float(J->table[threadIdx.x]);
-    }
-    // dynamic LDS: one f_n column per prefix node and thread (NPRE == 0
-    // only), then the prefix nodes' rows (pat_cap entries)
-    float2* s_pat = (float2*)(s_f + (NPRE > 0 ? (size_t)0 : (size_t)max(P->npre, 1) * WG));
-    const float2* pat = stage_prefix_rows<false>(P, s_pat, nullptr, pat_cap);
-    // a wave whose lanes all lie past the last unit has nothing to score (no
-    // barrier follows)
-    if (t0 + (threadIdx.x & ~63u) >= units) return;
-    float2 vyr[RY > 0 ? RY : 1];
-    if (RY > 0) {
-        const CS float2* aty = cs(P->aty);
-#pragma unroll
-        for (int iy = 0; iy < RY; ++iy) {
-            vyr[iy] = aty[iy];
-            if constexpr (YDIV) {
-                // only the durations are read in the loop; keep them in
-                // scalar registers (a reload per row would wait on the LDS
-                // reads too, both counting on lgkmcnt)
-                uint32_t v = __float_as_uint(vyr[iy].y);
-                asm volatile("" : "+s"(v));
-                vyr[iy].y = __uint_as_float(v);
-            }
-        }
-    }
-    __shared__ RareRow s_q[YDIV ? WG / 64 : 1][RQ];
-    RareRow* q = s_q[YDIV ? threadIdx.x >> 6 : 0];
-    uint32_t qn = 0;
-    const uint64_t live_mask = __ballot(live);
-    if constexpr (NPRE > 0) {
-        const PrefixHead ph = prefix_head<NPRE, false, RAD>(P, b0, J->big, pat, nullptr);
-        for (int g = 0; g < G; ++g)
-            sweep_block<HAS_S2, RY, NPRE, B256>(P, J, b0 + (uint64_t)g, live, prefix_tail<NPRE, false>(P, ph, g, pat, nullptr),
-                                                vyr, s_bins, s_f, q, qn, live_mask);
-    } else {
-        const Prefix pf = prefix_eval<NPRE, false, RAD>(P, b0, J->big, s_f, pat, nullptr);
-        sweep_block<HAS_S2, RY, NPRE, B256>(P, J, b0, live, pf, vyr, s_bins, s_f, q, qn, live_mask);
-    }
-    if (YDIV && qn) flush_rare<HAS_S2, NPRE>(P, J, q, qn, s_f);
-}
-
-// Work unit of sample j: one unit of the window [j S, min((j+1) S, n)), at a
-// hashed offset.  A fixed offset would alias with the mixed-radix digits (a
-// stride sharing factors with the radices visits only some implementation ids
-// of the low-order prefix nodes).
-__device__ __forceinline__ uint64_t sample_unit(uint64_t j, uint64_t S, uint64_t n) {
-    const uint64_t start = j * S;
-    const uint32_t width = (uint32_t)min(S, n - start);
-    const uint32_t h = (uint32_t)(j * 0x9E3779B1ull) >> 16;
-    return start + (uint64_t)(h % width);
 }
 
 // Seeding pre-pass of the sweep: work unit = one row (block, x-implementation)
@@ -1573,240 +855,6 @@ __device__ __forceinline__ ObjPlan obj_plan(const float2 vy, float dy, float M, 
     return ObjPlan{fmaf(nl, T, ux + vy.x), dx + dy};
 }
 
-template <bool HAS_S2, bool B256 = false>
-__device__ __forceinline__ uint64_t sweep_test_obj(const float2 vy, float dy, float M, float S2, float ux, float dx,
-                                                   float nl, uint32_t sh, const float* s_bins) {
-    const ObjPlan q = obj_plan<HAS_S2>(vy, dy, M, S2, ux, dx, nl);
-    const uint32_t off = B256 ? (__float_as_uint(q.D) >> 16) & 0x3fcu : (__float_as_uint(q.D) >> sh) & 0xfcu;
-    const float thr = *(const float*)((const char*)s_bins + off);
-    return __ballot(q.G >= thr);
-}
-
-// Objective mode, bin thresholds lowered ahead by each implementation j of y.
-// A row fixes ux (utility through x) and M (fp32 path into y without y's own
-// duration); its plan j has G = fma(-lambda_l, T, ux + u_j) with T =
-// max(fp32(tau_j + M), S2) >= fp32(tau_j + M), so, lambda_l being >= 0, G is
-// at most ux - lambda_l M + u_j - lambda_l tau_j plus the rounding of its
-// three operations, and R = fp32 fma(-lambda_l, M, ux) is at least ux -
-// lambda_l M less one rounding.  With c_j = P->ysub[j] >= u_j - lambda_l tau_j
-// + (a bound on those four roundings), a plan whose G reaches a bin threshold
-// t has R >= t - c_j.  Returned: the order key (fkey) of an fp32 value <= t -
-// c_j, so the row's test is skey(R) >= the least key of its plans' bins.
-// skey: the signed order key of a float (the magnitude bits of a negative
-// value flipped; -0 keys just below +0), three operations.
-__device__ __forceinline__ int32_t skey(float x) {
-    const int32_t b = __float_as_int(x);
-    return b ^ ((b >> 31) & 0x7fffffff);
-}
-
-__device__ __forceinline__ int32_t yshift_key(float t, float c) {
-    float x = t;
-    if (t != INFINITY && t != -INFINITY) {
-        x = t - c;  // nearest: within half an ulp of t - c
-        if (x != -INFINITY) {
-            const uint32_t b = __float_as_uint(x);
-            if (x > 0.0f) x = __uint_as_float(b - 1u);       // one ulp down (+inf: the largest finite)
-            else if (x < 0.0f) x = __uint_as_float(b + 1u);  // one ulp down
-        }
-        if (x == 0.0f) x = -0.0f;  // -0 keys below +0; a zero R (either sign) still passes
-    }
-    return skey(x);
-}
-
-// The rare path of the shifted sweep: the row's plans with the sweep's own
-// per-plan prefilter (G against its D bin's threshold, s_thr) and the exact
-// per-level test.
-template <bool HAS_S2>
-__device__ __forceinline__ void sweep_rare_obj(PD P, JD J, uint64_t b, int ix, float ux, float dx, float M, float S2,
-                                               const float* s_thr) {
-    const CS float2* aty = cs(P->aty);
-    const CS float* dyt = cs(P->demy);
-    const int ry = P->ry;
-    const float nl = -P->lam_l;
-    const uint64_t base = (b * (uint64_t)P->rx + (uint64_t)ix) * (uint64_t)ry;
-    for (int iy = 0; iy < ry; ++iy) {
-        const ObjPlan q = obj_plan<HAS_S2>(aty[iy], dyt[iy], M, S2, ux, dx, nl);
-        const float thr = *(const float*)((const char*)s_thr + ((__float_as_uint(q.D) >> 16) & 0x3fcu));
-        const uint64_t idx = base + (uint64_t)iy;
-        if (q.G >= thr && idx - J->begin < J->count && is_candidate_obj(P, J, q.G, q.D)) append_cand(J, idx, q.G, q.D);
-    }
-}
-
-// A row of the shifted sweep parked in its wave's queue (as RareRow).
-struct ObjRareRow {
-    uint64_t b;
-    uint32_t ix;
-    float ux, dx, M, S2;
-};
-
-template <bool HAS_S2>
-__device__ __forceinline__ void flush_rare_obj(PD P, JD J, const ObjRareRow* q, uint32_t n, const float* s_thr) {
-    const uint32_t lane = threadIdx.x & 63;
-    if (lane < n) {
-        const ObjRareRow e = q[lane];
-        sweep_rare_obj<HAS_S2>(P, J, e.b, (int)e.ix, e.ux, e.dx, e.M, e.S2, s_thr);
-    }
-}
-
-// The objective-mode inner sweep of block b (the prefix pf evaluated).  B256
-// with RY > 0: the shifted thresholds (s_bins: the 256 bin thresholds, then
-// RY x 256 keys of yshift_key), one test per row, rows that pass parked in q.
-template <bool HAS_S2, int RY, bool B256>
-__device__ __forceinline__ void sweep_block_obj(PD P, JD J, uint64_t b, bool live, const Prefix& pf,
-                                                const float2 (&vyr)[RY > 0 ? RY : 1],
-                                                const float (&dyr)[RY > 0 ? RY : 1], const float* s_bins,
-                                                ObjRareRow* q, uint32_t& qn, uint64_t live_mask) {
-    const uint32_t sh = (uint32_t)P->bin_shift - 2u;
-    const CS float2* atx = cs(P->atx);
-    const CS float2* aty = cs(P->aty);
-    const CS float* dxt = cs(P->demx);
-    const CS float* dyt = cs(P->demy);
-    const int rx = P->rx, ry = P->ry;
-    // without a second sink x is no sink, so it feeds y
-    const bool exy = !HAS_S2 || P->edge_xy != 0;
-    const float nl = -P->lam_l;
-    if constexpr (B256 && RY > 0) {
-        const int32_t* s_key = (const int32_t*)(s_bins + NBINS2);
-        for (int ix = 0; ix < rx; ++ix) {
-            const float2 vx = atx[ix];
-            const float fx = vx.y + pf.px;
-            const float ux = pf.pc + vx.x;
-            const float dx = pf.pd + dxt[ix];
-            const float M = exy ? fmaxf(pf.py, fx) : pf.py;
-            const float S2 = exy ? pf.s : fmaxf(pf.s, fx);
-            const float R = fmaf(nl, M, ux);
-            int32_t m = INT32_MAX;
-#pragma unroll
-            for (int j = 0; j < (RY > 0 ? RY : 1); ++j) {
-                const float D = dx + dyr[j];
-                m = min(m, *(const int32_t*)((const char*)(s_key + j * NBINS2) + ((__float_as_uint(D) >> 16) & 0x3fcu)));
-            }
-            const uint64_t hit = __ballot(skey(R) >= m) & live_mask;
-            if (hit) {
-                const uint32_t nh = (uint32_t)__popcll(hit);
-                if (qn + nh > (uint32_t)RQ) {
-                    flush_rare_obj<HAS_S2>(P, J, q, qn, s_bins);
-                    qn = 0;
-                }
-                const uint32_t lane = threadIdx.x & 63;
-                if (hit >> lane & 1ull) {
-                    const uint32_t o = qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32),
-                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0u));
-                    q[o] = ObjRareRow{b, (uint32_t)ix, ux, dx, M, S2};
-                }
-                qn += nh;
-            }
-        }
-        return;
-    }
-    for (int ix = 0; ix < rx; ++ix) {
-        const float2 vx = atx[ix];
-        const float fx = vx.y + pf.px;
-        const float ux = pf.pc + vx.x;
-        const float dx = pf.pd + dxt[ix];
-        const float M = exy ? fmaxf(pf.py, fx) : pf.py;
-        const float S2 = exy ? pf.s : fmaxf(pf.s, fx);
-        uint64_t hit = 0;
-        int iy = 0;
-        if (RY > 0) {
-#pragma unroll
-            for (int j = 0; j < (RY > 0 ? RY : 1); ++j)
-                hit |= sweep_test_obj<HAS_S2, B256>(vyr[j], dyr[j], M, S2, ux, dx, nl, sh, s_bins);
-            iy = ry;
-        }
-        for (; iy + 4 <= ry; iy += 4) {
-            const float2 v0 = aty[iy], v1 = aty[iy + 1], v2 = aty[iy + 2], v3 = aty[iy + 3];
-            const float d0 = dyt[iy], d1 = dyt[iy + 1], d2 = dyt[iy + 2], d3 = dyt[iy + 3];
-            hit |= sweep_test_obj<HAS_S2, B256>(v0, d0, M, S2, ux, dx, nl, sh, s_bins);
-            hit |= sweep_test_obj<HAS_S2, B256>(v1, d1, M, S2, ux, dx, nl, sh, s_bins);
-            hit |= sweep_test_obj<HAS_S2, B256>(v2, d2, M, S2, ux, dx, nl, sh, s_bins);
-            hit |= sweep_test_obj<HAS_S2, B256>(v3, d3, M, S2, ux, dx, nl, sh, s_bins);
-        }
-        for (; iy < ry; ++iy) hit |= sweep_test_obj<HAS_S2, B256>(aty[iy], dyt[iy], M, S2, ux, dx, nl, sh, s_bins);
-        if (hit) {
-            // rare: re-score this lane's row with the exact per-level test
-            const uint64_t base = (b * (uint64_t)rx + (uint64_t)ix) * (uint64_t)ry;
-            if (live && (hit >> (threadIdx.x & 63) & 1ull)) {
-                for (int iy = 0; iy < ry; ++iy) {
-                    const ObjPlan q = obj_plan<HAS_S2>(aty[iy], dyt[iy], M, S2, ux, dx, nl);
-                    const uint64_t idx = base + (uint64_t)iy;
-                    if (idx - J->begin < J->count && is_candidate_obj(P, J, q.G, q.D)) append_cand(J, idx, q.G, q.D);
-                }
-            }
-        }
-    }
-}
-
-// Work units as in k_sweep (runs of J->gblk blocks per thread with NPRE > 0);
-// B256: the 256 bins of D's pattern on shift 18 (one AND per plan).
-template <bool HAS_S2, int RY, int NPRE, bool B256 = false, int RAD = 0>
-__global__ void __launch_bounds__(WG) k_sweep_obj(const JobDev* __restrict__ jobs, uint64_t unit_off, int pat_cap) {
-    extern __shared__ float s_f[];
-    JD J = cs(jobs + blockIdx.y);
-    PD P = cs(J->prob);
-    const uint64_t units = J->units;
-    const int G = NPRE > 0 ? J->gblk : 1;
-    const uint64_t t0 = unit_off + (uint64_t)blockIdx.x * WG;
-    if (t0 >= units) return;
-    const uint64_t t = t0 + threadIdx.x;
-    const bool live = t < units;
-    const uint64_t b0 = J->blk_first + (live ? t : units - 1) * (uint64_t)G;
-    constexpr bool YSH = B256 && RY > 0;
-    __shared__ float s_bins[YSH ? (1 + (RY > 0 ? RY : 1)) * NBINS2 : (B256 ? NBINS2 : NBINS)];
-    if (B256) {
-        static_assert(!B256 || NBINS2 == WG, "one bin per thread");
-        const float thr = __uint_as_float(J->table2[threadIdx.x]);
-        s_bins[threadIdx.x] = thr;
-        if constexpr (YSH) {
-            int32_t* s_key = (int32_t*)(s_bins + NBINS2);
-#pragma unroll
-            for (int j = 0; j < (RY > 0 ? RY : 1); ++j) s_key[j * NBINS2 + threadIdx.x] = yshift_key(thr, P->ysub[j]);
-        }
-    } else if (threadIdx.x < NBINS) {
-        s_bins[threadIdx.x] = __uint_as_float(J->table[threadIdx.x]);
-    }
-    // dynamic LDS as in k_sweep, then the prefix nodes' d terms (pat_cap entries)
-    float2* s_pat = (float2*)(s_f + (NPRE > 0 ? (size_t)0 : (size_t)max(P->npre, 1) * WG));
-    float* s_pd = (float*)(s_pat + pat_cap);
-    const float2* pat = stage_prefix_rows<true>(P, s_pat, s_pd, pat_cap);
-    // a wave whose lanes all lie past the last unit has nothing to score (no
-    // barrier follows)
-    if (t0 + (threadIdx.x & ~63u) >= units) return;
-    float2 vyr[RY > 0 ? RY : 1];
-    float dyr[RY > 0 ? RY : 1];
-    if (RY > 0) {
-        const CS float2* aty = cs(P->aty);
-        const CS float* dyt = cs(P->demy);
-#pragma unroll
-        for (int iy = 0; iy < RY; ++iy) {
-            vyr[iy] = aty[iy];
-            dyr[iy] = dyt[iy];
-            if constexpr (YSH) {
-                // the shifted sweep reads only y's d terms; keep them in
-                // scalar registers
-                uint32_t v = __float_as_uint(dyr[iy]);
-                asm volatile("" : "+s"(v));
-                dyr[iy] = __uint_as_float(v);
-            }
-        }
-    }
-    __shared__ ObjRareRow s_q[YSH ? WG / 64 : 1][RQ];
-    ObjRareRow* q = s_q[YSH ? threadIdx.x >> 6 : 0];
-    uint32_t qn = 0;
-    const uint64_t live_mask = __ballot(live);
-    if constexpr (NPRE > 0) {
-        const PrefixHead ph = prefix_head<NPRE, true, RAD>(P, b0, J->big, pat, s_pd);
-        for (int g = 0; g < G; ++g)
-            sweep_block_obj<HAS_S2, RY, B256>(P, J, b0 + (uint64_t)g, live,
-                                              prefix_tail<NPRE, true>(P, ph, g, pat, s_pd), vyr, dyr, s_bins, q, qn,
-                                              live_mask);
-    } else {
-        const Prefix pf = prefix_eval<NPRE, true>(P, b0, J->big, s_f, pat, s_pd);
-        sweep_block_obj<HAS_S2, RY, B256>(P, J, b0, live, pf, vyr, dyr, s_bins, q, qn, live_mask);
-    }
-    if (YSH && qn) flush_rare_obj<HAS_S2>(P, J, q, qn, s_bins);
-}
-
 // Seeding pre-pass of the objective sweep: one hashed row per window of S
 // rows; per level the greatest fp32 estimate fma(-m_k, D, G) of a sampled plan
 // (every plan is admissible), reduced through DPP, LDS and an atomic max on
@@ -2126,9 +1174,6 @@ __global__ void __launch_bounds__(WG) k_scan(const JobDev* __restrict__ jobs, ui
 // certification: exact fp64 winner among the candidates (one WG per level)
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ bool better(double c1, uint64_t i1, double c2, uint64_t i2) {
-    return c1 > c2 || (c1 == c2 && i1 < i2);
-}
 
 // Wave-wide best (corr desc, index asc) through lane exchanges.
 __device__ __forceinline__ void wave_best(double& c, uint64_t& i) {
@@ -3131,68 +2176,6 @@ hipError_t launch_sample_sweep(const JobDev* d_jobs, int n, bool has_s2, bool ob
 #undef DYP_SAMPLE_NP
 #undef DYP_SAMPLE
     return hipGetLastError();
-}
-
-hipError_t launch_sweep(const JobDev* d_jobs, int n, bool has_s2, bool obj, uint64_t max_units, int npre_max,
-                        int npre_c, int ry, bool b256, bool rad12, int pat, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    // prefix rows staged in LDS: the group's largest table (npre x rmax
-    // entries), at least one entry, at most PAT_MAX (larger ones are read
-    // from global memory); f_n columns only without a compile-time prefix length
-    int pat_cap = std::min(std::max(pat, 1), PAT_MAX);
-    const bool fixed = npre_c == 2 || npre_c == 4 || npre_c == 6 || npre_c == 8;
-    const size_t lds = (fixed ? (size_t)0 : (size_t)(npre_max > 0 ? npre_max : 1) * WG * sizeof(float)) +
-                       (size_t)pat_cap * (sizeof(float2) + (obj ? sizeof(float) : 0));
-    for (uint64_t off = 0; off < max_units; off += MAX_GRID_X * WG) {
-        uint64_t left = max_units - off;
-        uint64_t gx = (left + WG - 1) / WG;
-        if (gx > MAX_GRID_X) gx = MAX_GRID_X;
-        const dim3 grid((uint32_t)gx, n);
-#define DYP_SWEEP(S2, RYV, NP)                                                                             \
-    do {                                                                                                   \
-        if (obj && b256 && rad12 && RYV == 12 && NP > 0)                                                   \
-            hipLaunchKernelGGL((k_sweep_obj<S2, RYV, NP, true, (RYV == 12 && NP > 0) ? 12 : 0>), grid, dim3(WG), \
-                               lds, s, d_jobs, off, pat_cap);                                              \
-        else if (obj && b256)                                                                              \
-            hipLaunchKernelGGL((k_sweep_obj<S2, RYV, NP, true, 0>), grid, dim3(WG), lds, s, d_jobs, off,   \
-                               pat_cap);                                                                   \
-        else if (obj)                                                                                      \
-            hipLaunchKernelGGL((k_sweep_obj<S2, RYV, NP>), grid, dim3(WG), lds, s, d_jobs, off, pat_cap); \
-        else if (b256 && rad12 && RYV == 12 && NP > 0)                                                     \
-            hipLaunchKernelGGL((k_sweep<S2, RYV, NP, true, (RYV == 12 && NP > 0) ? 12 : 0>), grid, dim3(WG), lds, \
-                               s, d_jobs, off, pat_cap);                                                   \
-        else if (b256)                                                                                     \
-            hipLaunchKernelGGL((k_sweep<S2, RYV, NP, true, 0>), grid, dim3(WG), lds, s, d_jobs, off, pat_cap); \
-        else                                                                                               \
-            hipLaunchKernelGGL((k_sweep<S2, RYV, NP, false, 0>), grid, dim3(WG), lds, s, d_jobs, off, pat_cap); \
-    } while (0)
-#define DYP_SWEEP_NP(S2, RYV)            \
-    switch (npre_c) {                    \
-        case 2: DYP_SWEEP(S2, RYV, 2); break; \
-        case 4: DYP_SWEEP(S2, RYV, 4); break; \
-        case 6: DYP_SWEEP(S2, RYV, 6); break; \
-        case 8: DYP_SWEEP(S2, RYV, 8); break; \
-        default: DYP_SWEEP(S2, RYV, 0); break; \
-    }
-        if (ry == 12) {
-            if (has_s2) {
-                DYP_SWEEP_NP(true, 12)
-            } else {
-                DYP_SWEEP_NP(false, 12)
-            }
-        } else {
-            if (has_s2) {
-                DYP_SWEEP_NP(true, 0)
-            } else {
-                DYP_SWEEP_NP(false, 0)
-            }
-        }
-#undef DYP_SWEEP_NP
-#undef DYP_SWEEP
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
 }
 
 hipError_t launch_sample_generic(const JobDev* d_jobs, int n, uint64_t max_samples, int ncol, hipStream_t s) {

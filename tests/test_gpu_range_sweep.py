@@ -1,0 +1,156 @@
+"""GPU parity of the range sweep that folds the last three nodes into tables.
+
+Against the fp64 oracle, at the sizes where its pieces change: one to four
+nodes (folded nodes missing), the last unrolled head and the first looped one,
+one implementation and the most a node can have, one and 32 levels, ranges
+that cut heads at both ends, one workgroup and several, several sinks, no edge
+between the last two nodes, unequal pressure, levels nothing meets.  Selections
+are decided in 64 bits, so the bar is equality.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import oracle as orc  # noqa: E402
+from paper_2607_02942_amd import dyplan as D  # noqa: E402
+from paper_2607_02942_amd import workload as wl  # noqa: E402
+
+from test_gpu_objective import assert_obj_choices  # noqa: E402
+from test_gpu_parity import assert_choices, stream  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    D.lib()
+    torch.cuda.set_device(0)
+    yield
+
+
+def problem(rng, radix, K, uniform, edge_p=0.4, tau_zero=False):
+    n, R = len(radix), max(radix)
+    edges = [(i, j) for i in range(n) for j in range(i + 1, n) if rng.random() < edge_p]
+    tau = rng.lognormal(0.0, 0.7, (n, R)).astype(np.float32)
+    if tau_zero:
+        tau[rng.random((n, R)) < 0.5] = 0.0
+    rho = np.sort(rng.uniform(0.0, 0.9, K))[:, None] * (np.ones((1, 2)) if uniform else rng.uniform(0.3, 1.0, (1, 2)))
+    prob = wl.Problem(n_nodes=n, edges=np.array(edges, np.int32).reshape(-1, 2), radix=np.array(radix, np.int32),
+                      p=rng.uniform(0.3, 1.0, (n, R)).astype(np.float32), tau=tau,
+                      size=np.ones((n, R), np.float32), backend=rng.integers(0, 2, (n, R)).astype(np.int32),
+                      w=rng.uniform(0.0, 1.0, n).astype(np.float32), rho=rho.astype(np.float32), slo=0.0)
+    # (for spaces beyond counting, the middle of a random sample's path lengths)
+    ids = [rng.integers(0, r, 999) for r in radix]
+    f = []
+    for v in range(n):
+        pr = [u for u, w in edges if w == v]
+        f.append(tau[v, ids[v]] + (np.max([f[u] for u in pr], axis=0) if pr else 0.0))
+    prob.slo = float(np.float32(np.median(np.max(f, axis=0)) * rng.uniform(0.6, 1.6)))
+    return prob
+
+
+SHAPES = {
+    "one": [7], "two": [5, 9], "three": [4, 1, 6], "four": [1, 3, 8, 5], "tools": [1, 1, 6, 1, 7, 1, 5, 1],
+    "wide_y": [3, 4, 255], "wide_x": [3, 255, 4], "wide_w": [2, 255, 3, 4], "wide_head": [255, 2, 3, 4],
+    "head8": [2, 3, 2, 2, 3, 2, 2, 2, 3, 4, 5], "head9": [2, 3, 2, 2, 2, 3, 2, 2, 2, 3, 4, 5],
+    "deep": [2] * 18, "six": [12] * 6, "big_table": [3, 2, 60, 40, 55, 3],
+}
+
+
+@pytest.mark.parametrize("mode", ["level", "class", "objective"])
+@pytest.mark.parametrize("shape", sorted(SHAPES))
+def test_shapes(shape, mode):
+    rng = np.random.default_rng([sorted(SHAPES).index(shape), len(mode)])
+    radix = SHAPES[shape]
+    for trial in range(4):
+        K = [1, 32, 5, 7][trial]
+        prob = problem(rng, radix, K, mode != "class", edge_p=[0.4, 0.0, 1.0, 0.5][trial], tau_zero=trial == 3)
+        total = prob.n_plans()
+        begin = int(rng.integers(0, max(1, total // 3))) if trial else 0
+        count = int(rng.integers(1, total - begin + 1)) if trial else total
+        srcs = [D.range_source(0, begin, count), D.range_source(0, total - 1, 1)]
+        ctx = f"{shape} {mode} trial {trial} [{begin}+{count}]"
+        if mode == "objective":
+            obj = wl.paper_objective(prob, levels=np.sort(rng.uniform(0, 4, K)), lambda_l=[0.05, 0.0, 0.4, 2.0][trial],
+                                     lambda_c=[0.01, 0.5, -0.1, 0.0][trial],
+                                     is_tool=(rng.random(len(radix)) < 0.3).astype(np.int32))
+            with D.Plan((prob, obj)) as plan:
+                got = plan.select(srcs, stream=stream())
+            for g, s in zip(got, srcs):
+                assert_obj_choices(g, orc.obj_select_range(prob, obj, s.begin, s.count), ctx)
+        else:
+            with D.Plan(prob) as plan:
+                got = plan.select(srcs, stream=stream())
+            for g, s in zip(got, srcs):
+                assert_choices(g, orc.select_range(prob, s.begin, s.count), ctx)
+
+
+@pytest.mark.parametrize("mode", ["level", "class", "objective"])
+def test_mixed_batch_repeats(mode):
+    # sources of different depths and sizes in one launch, some cut, one of
+    # several workgroups; repeated calls list the same candidates
+    rng = np.random.default_rng(5)
+    shapes = [[7], [5, 9], [6, 5, 4], [12] * 5, [2] * 15, [9, 8, 7, 6, 5, 4, 3], [20, 20, 20, 20, 5]]
+    probs = [problem(rng, r, 4, mode != "class") for r in shapes]
+    objs = [wl.paper_objective(p) for p in probs]
+    srcs, want = [], []
+    for j, p in enumerate(probs):
+        total = p.n_plans()
+        b = int(rng.integers(0, total))
+        for begin, count in ((0, total), (b, total - b)):
+            srcs.append(D.range_source(j, begin, count))
+            want.append(orc.obj_select_range(p, objs[j], begin, count) if mode == "objective"
+                        else orc.select_range(p, begin, count))
+    items = list(zip(probs, objs)) if mode == "objective" else probs
+    cands = []
+    with D.Plan(items) as plan:
+        for call in range(3):
+            got = plan.select(srcs, stream=stream())
+            cands.append(plan.stats().candidates)
+            for q, (g, w) in enumerate(zip(got, want)):
+                (assert_obj_choices if mode == "objective" else assert_choices)(g, w, f"{mode} call {call} source {q}")
+    assert len(set(cands)) == 1, cands
+
+
+def test_class_levels_out_of_order():
+    # durations of a later level below those of an earlier one, and levels
+    # whose bound no plan meets: each level's own sweep finds its choice
+    rng = np.random.default_rng(17)
+    for trial in range(6):
+        prob = problem(rng, [6, 5, 7, 4, 6], 6, False)
+        rho = rng.uniform(0.0, 0.95, (6, 2)).astype(np.float32)
+        rho[2] = 0.0
+        rho[4] = 0.995
+        prob = dataclasses.replace(prob, rho=rho)
+        total = prob.n_plans()
+        with D.Plan(prob) as plan:
+            got = plan.select([D.range_source(0, 0, total)], stream=stream())[0]
+        assert_choices(got, orc.select_range(prob, 0, total), f"trial {trial}")
+
+
+@pytest.mark.parametrize("slo", [0.0, 3.0e38, float("inf")])
+@pytest.mark.parametrize("uniform", [True, False])
+def test_extreme_bounds(slo, uniform):
+    prob = dataclasses.replace(problem(np.random.default_rng(3), [5, 6, 4, 3, 5], 4, uniform), slo=slo)
+    total = prob.n_plans()
+    with D.Plan(prob) as plan:
+        got = plan.select([D.range_source(0, 0, total), D.range_source(0, 17, 1000)], stream=stream())
+    assert_choices(got[0], orc.select_range(prob, 0, total), "whole")
+    assert_choices(got[1], orc.select_range(prob, 17, 1000), "part")
+
+
+def test_all_zero_durations_and_factors():
+    # every plan on one bin; factors of 0 (a plan of corr 0 is chosen)
+    prob = problem(np.random.default_rng(9), [4, 5, 6, 3], 3, True)
+    for p, w, tau in ((0.0, 1.0, 0.0), (0.5, 1.0, 0.0), (0.0, 1.0, 1.0)):
+        q = dataclasses.replace(prob, p=np.full_like(prob.p, p), w=np.full_like(prob.w, w),
+                                tau=np.full_like(prob.tau, tau), slo=10.0)
+        total = q.n_plans()
+        with D.Plan(q) as plan:
+            got = plan.select([D.range_source(0, 0, total)], stream=stream())[0]
+        assert_choices(got, orc.select_range(q, 0, total), f"p {p} tau {tau}")
