@@ -1849,11 +1849,12 @@ __global__ void __launch_bounds__(WG) k_score(const JobDev job, uint64_t unit_of
 
 // Per-plan scores of a RANGE source of 32-bit plan indices (uniform pressure
 // or the objective) by rows: a row fixes nodes 0..N-2 and its plans are node
-// y = N-1's implementations.  Phase 1: each lane takes one row and forms its
-// digits, prefix product (objective: sums), demand sum and the longest paths
-// into y and into the other sinks, once for the row.  Phase 2: the wave
-// scores the plans of its 64 rows, which are one contiguous span of plan
-// indices, 64 consecutive plans at a time; each plan adds y's terms to its
+// y = N-1's implementations.  A wave takes `span` consecutive outputs (a
+// multiple of 64, from a multiple of it) that at most 64 rows cover.  Phase 1:
+// each lane takes one row and forms its digits, prefix product (objective:
+// sums), demand sum and the longest paths into y and into the other sinks,
+// once for the row.  Phase 2: the wave scores the span, 64 consecutive plans at
+// a time; each plan adds y's terms to its
 // row's, in the same operations and order as the per-plan kernels.  Lane =
 // plan for the per-plan outputs; the K per-level values of the 64 plans are
 // stored lane-contiguously instead (each plan's scalars pass through LDS), so
@@ -1865,7 +1866,7 @@ __global__ void __launch_bounds__(WG) k_score(const JobDev job, uint64_t unit_of
 // Dynamic LDS: the recurrence column [N][WG] floats, the ids [N][WG], then the
 // (a, tau) and demand tables (N * R_max entries).
 template <bool OBJ>
-__global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t row_off, uint64_t row_end, float* corr,
+__global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t spans, uint32_t span, float* corr,
                                                   float* cpo, float* dem, uint32_t* feas) {
     extern __shared__ float s_dyn[];
     __shared__ uint32_t s_cert[NBINS2], s_chk[NBINS2];
@@ -1885,8 +1886,8 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t row
     const size_t head = (((size_t)N * WG * sizeof(float) + (size_t)N * WG) + 15) & ~(size_t)15;
     float2* s_at = (float2*)((char*)s_dyn + head);
     float* s_dm = (float*)(s_at + N * R);
-    const uint64_t first = row_off + (uint64_t)blockIdx.x * WG, stride = (uint64_t)gridDim.x * WG;
-    if (first >= row_end) return;
+    const uint64_t first = (uint64_t)blockIdx.x * (WG / 64), stride = (uint64_t)gridDim.x * (WG / 64);
+    if (first >= spans) return;
     for (int i = tid; i < N * R; i += WG) {
         s_at[i] = P->at[i];
         s_dm[i] = P->dem[i];
@@ -1916,16 +1917,17 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t row
         s_cert[tid] = cert;
         s_chk[tid] = chk;
     }
-    const uint64_t row0 = J->begin / (uint64_t)ry, p_end = J->begin + J->count;
+    const uint64_t count = J->count, last_row = (J->begin + count - 1) / (uint64_t)ry;
     const bool vec = cpo && (K & 3) == 0 && ((uintptr_t)cpo & 15) == 0;
     const uint32_t allk = K >= 32 ? 0xffffffffu : ((1u << K) - 1u);
     const uint32_t py = P->pred[y];
     const uint32_t kinv = (1u << 20) / (uint32_t)K + 1u;  // (f * kinv) >> 20 = f / K for f < 64 K, K <= 32
-    for (uint64_t base = first; base < row_end; base += stride) {
+    for (uint64_t base = first; base < spans; base += stride) {
         __syncthreads();  // tables staged; the previous batch's rows consumed
-        // phase 1: lane = row
-        const uint64_t rt = base + tid;
-        const uint64_t row = row0 + (rt < row_end ? rt : row_end - 1);
+        // phase 1: lane = row, from the row of the span's first plan
+        const uint64_t a0 = (base + (uint64_t)(tid >> 6)) * (uint64_t)span;  // the wave's first output
+        const uint64_t row0 = (J->begin + min(a0, count - 1)) / (uint64_t)ry;
+        const uint64_t row = min(row0 + (uint64_t)lane, last_row);
         uint32_t x = (uint32_t)row;
         for (int n = y - 1; n >= 0; --n) {
             const uint32_t q = mdiv(x, P->rmag[n]);
@@ -1952,25 +1954,22 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t row
         }
         s_pre[tid] = make_float4(cx, dx, M, S2);
         __syncthreads();
-        // phase 2: the wave's rows are rows r0 .. r0 + 63 (those below row_end),
-        // plans r0 ry .. (r0 + 64) ry - 1; 64 consecutive plans per step
-        const uint64_t wrow = base + (uint64_t)wbase;  // the wave's first row (relative to row0)
-        if (wrow >= row_end) continue;
-        const uint32_t nrows = (uint32_t)min((uint64_t)64, row_end - wrow);
-        const uint64_t pw = (row0 + wrow) * (uint64_t)ry;
-        for (uint32_t q0 = 0; q0 < nrows * (uint32_t)ry; q0 += 64) {
-            const uint32_t q = q0 + (uint32_t)lane;
+        // phase 2: 64 consecutive plans per step
+        if (a0 >= count) continue;
+        const uint32_t qa = (uint32_t)(J->begin + a0 - row0 * (uint64_t)ry);  // the span's first plan within its rows
+        const uint32_t n = (uint32_t)min((uint64_t)span, count - a0);
+        for (uint32_t s0 = 0; s0 < n; s0 += 64) {
+            const uint32_t q = qa + min(s0 + (uint32_t)lane, n - 1);
             const uint32_t lr = mdiv(q, P->rmag[y]);  // local row
             const int j = (int)(q - lr * (uint32_t)ry);
-            const uint64_t p = pw + q;
-            const bool live = lr < nrows && p >= J->begin && p < p_end;
-            const float4 pr = s_pre[wbase + (int)min(lr, nrows - 1)];
+            const uint64_t o = a0 + s0 + (uint64_t)lane;
+            const bool live = s0 + (uint32_t)lane < n;
+            const float4 pr = s_pre[wbase + (int)lr];
             const int e = y * R + j;
             const float2 v = s_at[e];
             const float cc = OBJ ? pr.x + v.x : pr.x * v.x;
             const float d = pr.y + s_dm[e];
             const float cp0 = fmaxf(v.y + pr.z, pr.w);
-            const uint64_t o = p - J->begin;
             float G = 0.0f;
             uint32_t bits = allk;
             if (OBJ) {
@@ -1994,7 +1993,7 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t row
                     // over s_f (free in this phase): its row's digits, which phase 1
                     // left in the row's column of s_id, and y's id
                     uint8_t* s_pid = (uint8_t*)s_f;
-                    const int rc = wbase + (int)min(lr, nrows - 1);
+                    const int rc = wbase + (int)lr;
                     for (int n = 0; n < y; ++n) s_pid[n * WG + tid] = s_id[n * WG + rc];
                     s_pid[y * WG + tid] = (uint8_t)j;
                     __builtin_amdgcn_wave_barrier();
@@ -2014,16 +2013,13 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t row
             // store covers one contiguous span
             s_v[tid] = make_float2(OBJ ? G : cp0, d);
             __builtin_amdgcn_wave_barrier();
-            const uint32_t nlive = (uint32_t)min((uint64_t)nrows * (uint64_t)ry - q0, (uint64_t)64);
-            const uint64_t p0 = pw + q0;  // plan of the step's first lane
-            const uint32_t la = p0 < J->begin ? (uint32_t)(J->begin - p0) : 0u;
-            const uint32_t lb = p0 >= p_end ? 0u : (uint32_t)min((uint64_t)nlive, p_end - p0);
-            const int64_t e0 = ((int64_t)p0 - (int64_t)J->begin) * K;  // output float of the step's lane 0 (>= 0 from lane la on)
+            const uint32_t lb = min(n - s0, 64u);
+            const uint64_t e0 = (a0 + s0) * (uint64_t)K;  // output float of the step's lane 0
             if (vec) {
                 for (int m = 0; m < K; m += 4) {
                     const uint32_t f = 4u * (uint32_t)lane + 64u * (uint32_t)m;  // float within the 64 rows
                     const uint32_t pl = (f * kinv) >> 20, k = f - pl * (uint32_t)K;
-                    if (pl < la || pl >= lb) continue;
+                    if (pl >= lb) continue;
                     const float2 u = s_v[wbase + (int)pl];
                     const float4 c = *(const float4*)(s_mk + k);
                     const float4 w = OBJ ? make_float4(fmaf(-c.x, u.y, u.x), fmaf(-c.y, u.y, u.x), fmaf(-c.z, u.y, u.x),
@@ -2035,7 +2031,7 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t row
                 for (int m = 0; m < K; ++m) {
                     const uint32_t f = (uint32_t)lane + 64u * (uint32_t)m;
                     const uint32_t pl = (f * kinv) >> 20, k = f - pl * (uint32_t)K;
-                    if (pl < la || pl >= lb) continue;
+                    if (pl >= lb) continue;
                     const float2 u = s_v[wbase + (int)pl];
                     cpo[e0 + f] = OBJ ? fmaf(-s_mk[k], u.y, u.x) : u.x * s_mk[k];
                 }
@@ -2259,23 +2255,30 @@ hipError_t launch_score(const JobDev& job, uint64_t units, float* corr, float* c
     const size_t head = (((size_t)n_nodes * WG * sizeof(float) + (size_t)n_nodes * WG) + 15) & ~(size_t)15;
     const size_t lds_row = head + (size_t)n_entries * (sizeof(float2) + sizeof(float));
     if (simple && job.kind == DY_SOURCE_RANGE && !job.big && n_entries <= SCORE_ROW_TAB && lds_row <= SCORE_ROW_LDS) {
-        const uint64_t rows = (job.begin + job.count - 1) / (uint64_t)ry - job.begin / (uint64_t)ry + 1;
-        for (uint64_t off = 0; off < rows; off += MAX_GRID_X * WG) {
-            const uint64_t end = rows - off < MAX_GRID_X * WG ? rows : off + MAX_GRID_X * WG;
-            const uint64_t gx = (end - off + WG * SCORE_ROWS_PT - 1) / (WG * SCORE_ROWS_PT);
+        // outputs per wave: those of 64 rows where such spans begin at a
+        // row, else as many times 64 as 64 rows cover from anywhere in the
+        // first (every line of the outputs is then written by one store: 2^26
+        // forkjoin8 plans from plan 12345 took 757 us in steps of 64 plans from
+        // a row's first, 538 us so)
+        uint32_t span = 64u * (uint32_t)ry;
+        if (job.begin % (uint64_t)ry != 0) span = 64u * std::max(1u, (62u * (uint32_t)ry + 1u) / 64u);
+        const uint64_t spans = (job.count + span - 1) / span;
+        const uint64_t per = (uint64_t)(WG / 64) * SCORE_ROWS_PT;
+        {
+            const uint64_t gx = std::min<uint64_t>((spans + per - 1) / per, MAX_GRID_X);
             if (obj)
-                hipLaunchKernelGGL(k_score_row<true>, dim3((uint32_t)gx), dim3(WG), lds_row, s, job, off, end, corr, cp,
-                                   dem, feas);
+                hipLaunchKernelGGL(k_score_row<true>, dim3((uint32_t)gx), dim3(WG), lds_row, s, job, spans, span, corr,
+                                   cp, dem, feas);
             else
-                hipLaunchKernelGGL(k_score_row<false>, dim3((uint32_t)gx), dim3(WG), lds_row, s, job, off, end, corr, cp,
-                                   dem, feas);
+                hipLaunchKernelGGL(k_score_row<false>, dim3((uint32_t)gx), dim3(WG), lds_row, s, job, spans, span, corr,
+                                   cp, dem, feas);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
     }
-    // everything else (rows, per-backend pressure, 64-bit indices, large
-    // tables): the generic per-plan kernel
+    // everything else (rows without a generated kernel, 64-bit indices, tables
+    // too large for LDS): the generic per-plan kernel
     for (uint64_t off = 0; off < units; off += MAX_GRID_X * WG) {
         const uint64_t end = units - off < MAX_GRID_X * WG ? units : off + MAX_GRID_X * WG;
         const uint64_t gx = (end - off + WG * SCORE_PPT - 1) / (WG * SCORE_PPT);
