@@ -44,6 +44,8 @@ struct JitRows {
 };
 bool jit_rows_get(int device, const ProbDev& D, JitRows* out, std::string* err);
 std::string jit_rows_source(const ProbDev& D);
+hipError_t launch_score_class(const JobDev& job, uint64_t units, float* corr, float* cp, float* dem, uint32_t* feas,
+                              int n_nodes, int n_entries, int levels, hipStream_t s) __attribute__((weak));
 hipError_t launch_score(const JobDev& job, uint64_t units, float* corr, float* cp, float* dem, uint32_t* feas,
                         int n_nodes, int n_entries, int ry, bool simple, bool obj, hipStream_t s);
 }  // namespace dyp
@@ -2013,11 +2015,13 @@ int dy_plan_score(dy_plan* h, const dy_source* src, float* corr, float* cp, floa
     hipError_t e;
     // RANGE sources of 32-bit indices (uniform pressure or the objective) take
     // the library's row kernel (the prefix once per row of y's plans); rows,
-    // the problem's generated kernel when it compiles; everything else the
-    // generic per-plan kernel
+    // the problem's generated kernel when it compiles; per-backend pressure the
+    // library's kernel of four levels at a time, whose tables must fit LDS;
+    // everything else the generic per-plan kernel
     if (src->kind == DY_SOURCE_ROWS && simple && jit_ready(h, src->problem) && h->jit[src->problem].score_rows)
         e = launch_jit_score(h, src->problem, *src, corr, cp, demand, feas_bits, (hipStream_t)stream);
-    else
+    else if (simple || (e = launch_score_class(J, src->count, corr, cp, demand, feas_bits, H.n, H.n * H.rmax, H.k,
+                                               (hipStream_t)stream)) == hipErrorNotSupported)
         e = launch_score(J, src->count, corr, cp, demand, feas_bits, H.n, H.n * H.rmax, H.ry, simple, D.obj != 0,
                          (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(&h->err, e, "score launch");

@@ -1680,6 +1680,8 @@ constexpr int SCORE_TAB_N = 12;
 // staged tables.
 constexpr uint64_t SCORE_PPT = 8;  // plans per thread of k_score (the tables are staged once per block)
 constexpr int SCORE_ROW_TAB = 2048;      // table entries (N x R_max) of k_score_row, staged in LDS
+constexpr size_t SCORE_CLASS_LAT = 40 << 10;  // durations that k_score_class stages in LDS at most
+constexpr size_t SCORE_CLASS_LDS = 64 << 10;  // its dynamic LDS at most
 constexpr size_t SCORE_ROW_LDS = 56 << 10;  // its dynamic LDS at most (64 KiB with the static arrays)
 constexpr uint64_t SCORE_ROWS_PT = 2;    // rows per thread of k_score_row
 
@@ -2041,6 +2043,208 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t spa
     }
 }
 
+// Per-plan scores under per-backend pressure (rows or a range; DAGs of at most
+// NN nodes).  Bound by the recurrences: every level has its own, K N adds and
+// K E maxima a plan.  Lane = plan; four levels advance together, with the four
+// paths into every node in registers (the unrolled predecessor tests are
+// wave-uniform branches, paid once for four levels), and one 16-byte LDS read
+// gives a node's four durations.  The durations of KC levels (8, or 4 for large
+// tables) are staged at a time, once per workgroup when they are all; the KC
+// values of each of a wave's 64 plans pass through LDS, so stores cover
+// contiguous spans.  2^20 rows of 24 nodes at 8 levels: 520 us by the generic
+// kernel (one level at a time, its recurrence column in LDS), 132 us by this
+// one; without the reads one node ahead and with four rounds of workgroups, 184.
+// Dynamic LDS: durations [N * R_max][KC], the per-level values [WG][KC], (a,
+// demand) [N * R_max], the ids [N][WG] (for resolve_bands).
+template <int NN>
+__global__ void __launch_bounds__(WG) k_score_class(const JobDev job, uint64_t unit_off, uint64_t unit_end, float* corr,
+                                                    float* cpo, float* dem, uint32_t* feas, int KC, int words) {
+    extern __shared__ __align__(16) char s_raw[];
+    JD J = cs(&job);
+    PD P = cs(J->prob);
+    const int N = P->n, R = P->rmax, K = P->k, tid = threadIdx.x, lane = tid & 63, wbase = tid & ~63;
+    const int NR = N * R;
+    // (read back per node: 32 masks and radices in scalar registers spill)
+    __shared__ uint32_t s_pred[NMAX], s_radix[NMAX];
+    float* s_lat = (float*)s_raw;
+    float* s_cp = s_lat + (size_t)NR * KC;
+    float2* s_ad = (float2*)(s_cp + (size_t)WG * KC);
+    uint8_t* s_id = (uint8_t*)(s_ad + NR);
+    const uint64_t first = unit_off + (uint64_t)blockIdx.x * WG, stride = (uint64_t)gridDim.x * WG;
+    if (first >= unit_end) return;
+    for (int i = tid; i < NR; i += WG) s_ad[i] = make_float2(P->at[i].x, P->dem[i]);
+    auto stage = [&](int k0) {
+        for (int i = tid; i < NR * KC; i += WG) {
+            const int e = i / KC, k = k0 + i - e * KC;
+            s_lat[i] = k < K ? P->lat[(size_t)k * NR + e] : 0.0f;
+        }
+    };
+    const bool all = K <= KC;
+    if (all) stage(0);
+    if (tid < N) {
+        s_pred[tid] = P->pred[tid];
+        s_radix[tid] = (uint32_t)P->radix[tid];
+    }
+    const uint32_t sinks = P->sinks;
+    __syncthreads();
+    const float glo = P->glo, ghi = P->ghi;
+    for (uint64_t base = first; base < unit_end; base += stride) {
+        const uint64_t t = base + tid;
+        const bool live = t < unit_end;
+        const uint64_t r = live ? t : unit_end - 1;
+        // ids, four to a register
+        uint32_t w[NN / 4];
+        bool bad = false;
+        if (J->kind == DY_SOURCE_RANGE) {
+            uint64_t x = J->begin + r;
+#pragma unroll
+            for (int q = 0; q < NN / 4; ++q) w[q] = 0u;
+#pragma unroll
+            for (int n = NN - 1; n >= 0; --n)
+                if (n < N) {
+                    uint32_t d;
+                    if (x <= 0xffffffffull) {
+                        const uint32_t q = mdiv((uint32_t)x, P->rmag[n]);
+                        d = (uint32_t)x - q * (uint32_t)P->radix[n];
+                        x = q;
+                    } else {
+                        const uint64_t rr = (uint64_t)P->radix[n];
+                        d = (uint32_t)(x % rr);
+                        x /= rr;
+                    }
+                    w[n / 4] |= d << (8 * (n & 3));
+                }
+        } else {
+            const uint8_t* row = J->rows + r * J->stride;
+#pragma unroll
+            for (int q = 0; q < NN / 4; ++q) {
+                w[q] = 0u;
+                if (words) {
+                    if (4 * q < N) w[q] = ((const uint32_t*)row)[q];
+                } else {
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        if (4 * q + b < N) w[q] |= (uint32_t)row[4 * q + b] << (8 * b);
+                }
+            }
+#pragma unroll
+            for (int n = 0; n < NN; ++n)
+                if (n < N && (w[n / 4] >> (8 * (n & 3)) & 255u) >= s_radix[n]) {
+                    bad = true;  // read as 0: NaN scores, no feasible level
+                    w[n / 4] &= ~(255u << (8 * (n & 3)));
+                }
+        }
+        const bool out = live && !bad;
+        float cc = 1.0f, d = 0.0f;
+#pragma unroll
+        for (int n = 0; n < NN; ++n)
+            if (n < N) {
+                const float2 v = s_ad[n * R + (int)(w[n / 4] >> (8 * (n & 3)) & 255u)];
+                cc = cc * v.x;
+                d = d + v.y;
+            }
+        uint32_t bits = 0, amb = 0;
+        for (int k0 = 0; k0 < K; k0 += KC) {
+            if (!all) {
+                __syncthreads();  // the previous levels' readers are done
+                stage(k0);
+                __syncthreads();
+            }
+            for (int c = 0; c < KC && k0 + c < K; c += 4) {
+                // (paths are not negative: their patterns order as they do, and
+                // an integer maximum needs no NaN quieting)
+                uint4 f[NN], cp = make_uint4(0u, 0u, 0u, 0u);
+                auto up = [](uint4& a, const uint4& b) {
+                    a.x = max(a.x, b.x);
+                    a.y = max(a.y, b.y);
+                    a.z = max(a.z, b.z);
+                    a.w = max(a.w, b.w);
+                };
+                auto add = [](float a, uint32_t b) { return __float_as_uint(a + __uint_as_float(b)); };
+                // the loop-invariant tests below stay where they are (hoisted, 24
+                // of them fill the scalar registers)
+                int Nv = N;
+                uint32_t sv = sinks;
+                asm volatile("" : "+s"(Nv), "+s"(sv));
+                // a node's durations and predecessors are read while the one
+                // before it is worked on
+                auto durations = [&](int n) __attribute__((always_inline)) {
+                    return *(const float4*)(s_lat + (n * R + (int)(w[n / 4] >> (8 * (n & 3)) & 255u)) * KC + c);
+                };
+                float4 next = durations(0);
+                uint32_t pnext = s_pred[0];
+#pragma unroll
+                for (int n = 0; n < NN; ++n)
+                    if (n < Nv) {
+                        const float4 l = next;
+                        const uint32_t pm = (uint32_t)__builtin_amdgcn_readfirstlane((int)pnext);
+                        if (n + 1 < NN && n + 1 < Nv) {
+                            next = durations(n + 1 < NN ? n + 1 : 0);
+                            pnext = s_pred[n + 1];
+                        }
+                        uint4 m = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+                        for (int u = 0; u < n; ++u)
+                            if (pm >> u & 1u) up(m, f[u]);
+                        f[n] = make_uint4(add(l.x, m.x), add(l.y, m.y), add(l.z, m.z), add(l.w, m.w));
+                        if (sv >> n & 1u) up(cp, f[n]);
+                    }
+                const float4 cv = make_float4(__uint_as_float(cp.x), __uint_as_float(cp.y), __uint_as_float(cp.z),
+                                              __uint_as_float(cp.w));
+                const float v[4] = {cv.x, cv.y, cv.z, cv.w};
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int k = k0 + c + b;
+                    if (k < K) {
+                        if (v[b] <= glo)
+                            bits |= 1u << k;
+                        else if (v[b] <= ghi)
+                            amb |= 1u << k;
+                    }
+                }
+                if (cpo)
+                    *(float4*)(s_cp + (size_t)tid * KC + c) =
+                        out ? cv : make_float4(NAN, NAN, NAN, NAN);
+            }
+            if (cpo) {
+                __builtin_amdgcn_wave_barrier();
+                // the wave's 64 plans, kn values each
+                const uint32_t kn = (uint32_t)min(KC, K - k0);
+                const uint64_t t0 = base + (uint64_t)wbase;
+                const uint32_t nl = t0 < unit_end ? (uint32_t)min((uint64_t)64, unit_end - t0) : 0u;
+                const float* s_w = s_cp + (size_t)wbase * KC;
+                if ((kn & 3u) == 0 && (K & 3) == 0 && ((uintptr_t)cpo & 15) == 0) {
+                    const uint32_t kq = kn / 4;
+                    for (uint32_t i = (uint32_t)lane; i < nl * kq; i += 64) {
+                        const uint32_t pl = i / kq, c = 4u * (i - pl * kq);
+                        *(float4*)(cpo + (t0 + pl) * (uint64_t)K + (uint64_t)k0 + c) = *(const float4*)(s_w + pl * KC + c);
+                    }
+                } else {
+                    for (uint32_t i = (uint32_t)lane; i < nl * kn; i += 64) {
+                        const uint32_t pl = i / kn, c = i - pl * kn;
+                        cpo[(t0 + pl) * (uint64_t)K + (uint64_t)k0 + c] = s_w[pl * KC + c];
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        if (!out) amb = 0u;
+        if (feas && __ballot(amb != 0u)) {  // a CP inside the band: the definition's fp64 value decides
+#pragma unroll
+            for (int n = 0; n < NN; ++n)
+                if (n < N) s_id[n * WG + tid] = (uint8_t)(w[n / 4] >> (8 * (n & 3)));
+            __builtin_amdgcn_wave_barrier();
+            resolve_bands(P, s_id, amb, &bits);
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (live) {
+            if (corr) corr[t] = out ? cc : NAN;
+            if (feas) feas[t] = out ? bits : 0u;
+            if (dem) dem[t] = out ? d : NAN;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // launch wrappers (host)
 // ---------------------------------------------------------------------------
@@ -2287,6 +2491,32 @@ hipError_t launch_score(const JobDev& job, uint64_t units, float* corr, float* c
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// Per-plan scores under per-backend pressure; hipErrorNotSupported (nothing
+// launched) where the tables do not fit LDS.
+hipError_t launch_score_class(const JobDev& job, uint64_t units, float* corr, float* cp, float* dem, uint32_t* feas,
+                              int n_nodes, int n_entries, int levels, hipStream_t s) {
+    const size_t e4 = (size_t)n_entries * sizeof(float);
+    const int KC = e4 * 8 <= SCORE_CLASS_LAT ? std::min(8, (levels + 3) / 4 * 4) : 4;
+    const size_t lds = e4 * KC + (size_t)WG * KC * sizeof(float) + (size_t)n_entries * sizeof(float2) + (size_t)n_nodes * WG;
+    if (e4 * KC > SCORE_CLASS_LAT || lds > SCORE_CLASS_LDS) return hipErrorNotSupported;
+    const int words =
+        job.kind == DY_SOURCE_ROWS && ((job.stride | (uint64_t)(uintptr_t)job.rows | (uint64_t)n_nodes) & 3u) == 0 ? 1 : 0;
+    // one resident round of workgroups, which stage the tables once (by the
+    // registers of the unrolled recurrence four, three or two to a CU)
+    const uint64_t round = n_nodes <= 8 ? 1024 : n_nodes <= 16 ? 768 : 512;
+    const uint64_t gx = std::min<uint64_t>((units + WG - 1) / WG, round);
+    const dim3 g((uint32_t)gx);
+    if (n_nodes <= 8)
+        hipLaunchKernelGGL(k_score_class<8>, g, dim3(WG), lds, s, job, 0, units, corr, cp, dem, feas, KC, words);
+    else if (n_nodes <= 16)
+        hipLaunchKernelGGL(k_score_class<16>, g, dim3(WG), lds, s, job, 0, units, corr, cp, dem, feas, KC, words);
+    else if (n_nodes <= 24)
+        hipLaunchKernelGGL(k_score_class<24>, g, dim3(WG), lds, s, job, 0, units, corr, cp, dem, feas, KC, words);
+    else
+        hipLaunchKernelGGL(k_score_class<32>, g, dim3(WG), lds, s, job, 0, units, corr, cp, dem, feas, KC, words);
+    return hipGetLastError();
 }
 
 }  // namespace dyp
