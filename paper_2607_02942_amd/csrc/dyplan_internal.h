@@ -122,6 +122,7 @@ struct ProbDev {
     // of the nodes' largest durations), and per node the share of a unit flow
     // from the sources to the sinks that passes through it, split evenly at forks
     float lam0;
+    float u_top;              // objective mode: the largest u
     float flow[NMAX];
     // Per-backend pressure, per level: least fp32 CP_k, bin shift of [cplo,
     // ghi], least contributions of y, of x and y, and of w and what follows;
@@ -187,6 +188,7 @@ struct JobDev {
     uint32_t* wk;             // [SOLVE_WK]
     int32_t nwg;
     int32_t seeded;
+    int32_t whole;            // the range is the whole plan space
 };
 
 

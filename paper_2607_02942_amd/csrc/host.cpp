@@ -982,6 +982,9 @@ int stage_problems(dy_plan* h, const dy_problem* probs, int32_t n_probs, std::st
                 sum += (double)m;
                 roots += D.pred[n] == 0;
             }
+            D.u_top = -INFINITY;
+            for (int n = 0; n < N; ++n)
+                for (int i = 0; i < pb.radix[n]; ++i) D.u_top = std::max(D.u_top, at[(size_t)n * R + i].x);
             D.lam0 = sum > 0.0 ? (float)std::min(3.0 * N / sum, 1e30) : 0.0f;
             int out[DY_MAX_NODES] = {};
             for (int n = 0; n < N; ++n)
@@ -1485,6 +1488,7 @@ void split_source(JobDev& J, const ProbDev& D, uint64_t share) {
     const uint64_t rw = D.npre > 0 ? (uint64_t)D.radix[D.npre - 1] : 1;
     J.ublk0 = J.blk_first / rw;
     J.units = (J.blk_first + J.nblk - 1) / rw - J.ublk0 + 1;
+    J.whole = J.begin == 0 && J.count == D.n_plans ? 1 : 0;
     uint64_t p0 = J.begin, p1 = J.begin + J.count - 1;
     for (int n = D.n - 1; n >= 0; --n) {
         const uint64_t r = (uint64_t)D.radix[n];

@@ -41,13 +41,14 @@ constexpr int SOLVE_HEAD = 8;      // longest unrolled head
 constexpr int SOLVE_Q = 320;       // queue entries (a round adds at most WG; drained above SOLVE_Q - WG)
 constexpr int SOLVE_PAIRS = 1280;  // (candidate, level) pairs gathered per certification round
 constexpr int SOLVE_REBUILD = 512; // rows unfolded before the tables are rebuilt on the raised seeds
+constexpr int SOLVE_OWN = 32;      // candidates kept in LDS as well
 constexpr int SOLVE_LAT = 4096;    // per-backend pressure: durations of all levels kept in LDS for the seeding up to this many
 
 enum { SV_LEVEL = 0, SV_CLASS = 1, SV_OBJ = 2 };
 
 // Dynamic LDS, in bytes from its start.  The certification reuses all of it.
 struct SolveLds {
-    int at, dm, ln, e3, q3, d3, col, sc, lat, hx, hv, bq, rq, total;
+    int at, dm, e3, q3, d3, col, sc, nt, lat, hx, hv, bq, rq, total;
 };
 
 __host__ __device__ inline SolveLds solve_lds(int ent, int rmax, int nlat, int ncol, int nmax, bool obj) {
@@ -60,13 +61,13 @@ __host__ __device__ inline SolveLds solve_lds(int ent, int rmax, int nlat, int n
     };
     L.at = take(ent * 8);                // every node's (a, tau) (objective: (u, tau))
     L.dm = take(obj ? ent * 4 : 0);      // objective: every node's d
-    L.ln = take(obj ? 0 : ent * 4);      // corr: every factor's logarithm (seeding)
     L.e3 = take(3 * rmax * 8);           // (a, tau) of w, x and y
     L.q3 = take(3 * rmax * 8);           // reciprocal factors of w, x and y (objective: two offsets each)
     L.d3 = take(obj ? 3 * rmax * 4 : 0); // objective: d of w, x and y
     L.col = take(ncol * WG * 4);         // recurrence columns
     L.sc = o;                            // seeding only, where the queues follow: a recurrence column per node,
-    L.lat = o + nmax * WG * 4;           // and (per-backend pressure) the durations at every level
+    L.nt = o + nmax * WG * 4;            // every node's (-ln a, tau) (objective: (u_max - u, tau)),
+    L.lat = L.nt + ent * 8;              // and (per-backend pressure) the durations at every level
     L.hx = take(SOLVE_Q * 8);            // parked heads: index, then product, paths, (sum of d)
     L.hv = take(SOLVE_Q * 4 * (obj ? 6 : 5));
     L.bq = take(SOLVE_Q * 4);            // parked blocks: head slot, w
@@ -353,9 +354,14 @@ __device__ __forceinline__ bool row_test(const SV& S, const SRow& r) {
 
 // Append to the source's candidate list: the workgroup's count is n (LDS), the
 // source's, where it has several, in device memory.
-__device__ __forceinline__ void solve_append(JD J, LS uint32_t* n, uint64_t index, float c, float cp) {
+__device__ __forceinline__ void solve_append(JD J, LS uint32_t* n, LS Cand* own, uint64_t index, float c, float cp) {
     uint32_t slot = __hip_atomic_fetch_add(n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (J->nwg > 1) slot = atomicAdd(J->wk, 1u);
+    if (slot < (uint32_t)SOLVE_OWN) {  // (read back from here by a source's only workgroup)
+        own[slot].index = index;
+        own[slot].corr = c;
+        own[slot].cp = cp;
+    }
     if (slot < J->cap) {
         Cand* d = J->cand + slot;
         d->index = index;
@@ -390,7 +396,7 @@ __device__ __forceinline__ float plain_cp(const SV& S, uint64_t b, int big, int 
 // the level kk of the pass.
 template <int MODE, class SV>
 __device__ __forceinline__ void plan_exact(const SV& S, uint64_t b, int big, int ix, const SRow& r, int j, int kk,
-                                           LS uint32_t* s_seed, LS uint32_t* n) {
+                                           LS uint32_t* s_seed, LS uint32_t* n, LS Cand* own) {
     PD P = S.P;
     JD J = S.J;
     const uint64_t idx = (b * (uint64_t)P->rx + (uint64_t)ix) * (uint64_t)P->ry + (uint64_t)j;
@@ -406,14 +412,14 @@ __device__ __forceinline__ void plan_exact(const SV& S, uint64_t b, int big, int
                 cand = true;
                 raise_seed(s_seed + k, fkey(fmaf(-P->m32[k], D, G)));
             }
-        if (cand) solve_append(J, n, idx, G, D);
+        if (cand) solve_append(J, n, own, idx, G, D);
         return;
     }
     const float c = r.c * v.x;
     if (MODE == SV_CLASS) {
         if (T <= P->ghi && c >= S.s_thr[kk]) {
             if (T <= P->glo) raise_seed(s_seed + kk, __float_as_uint(c) + 1u);
-            solve_append(J, n, idx, c, plain_cp(S, b, big, ix, j));
+            solve_append(J, n, own, idx, c, plain_cp(S, b, big, ix, j));
         }
         return;
     }
@@ -422,7 +428,7 @@ __device__ __forceinline__ void plan_exact(const SV& S, uint64_t b, int big, int
             cand = true;
             if (T <= S.s_lo[k]) raise_seed(s_seed + k, __float_as_uint(c) + 1u);
         }
-    if (cand) solve_append(J, n, idx, c, T);
+    if (cand) solve_append(J, n, own, idx, c, T);
 }
 
 // fp64 corr, CP and demand (objective: U, T, D) of candidate ids, as cert_eval
@@ -479,8 +485,11 @@ __device__ __forceinline__ void pair_eval(PD P, const uint8_t* ids, double* f, i
 // thresholds (every workgroup of a source the same) and building the tables.
 // The workgroup that ends last certifies the candidates in fp64 and writes
 // the choices.
+// Five waves per SIMD: with one more register group the batches, whose
+// workgroups wait on LDS chains most of the time, ran 9 % longer; at six (80
+// registers, spills) small sources run 3 to 10 % longer.
 template <int MODE>
-__global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, int ent, int rmax_all, int nlat,
+__global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs, int ent, int rmax_all, int nlat,
                                               int ncol, int nf, int lds) {
     constexpr bool OBJ = MODE == SV_OBJ;
     constexpr int NB = OBJ ? SOLVE_BINS_OBJ : SOLVE_BINS, Q = NB / WG;
@@ -490,6 +499,7 @@ __global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, i
     __shared__ uint32_t s_seed[KMAX];
     __shared__ uint8_t s_b0[NMAX], s_b1[NMAX];
     __shared__ uint32_t s_cnt[WG / 64];
+    __shared__ Cand s_own[SOLVE_OWN];
     __shared__ uint32_t s_nh, s_nb, s_nr, s_nc, s_flag, s_rows;
     JD J = cs(jobs + blockIdx.y);
     PD P = cs(J->prob);
@@ -544,10 +554,8 @@ __global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, i
         for (int i = tid; i < N * R; i += WG) {
             const float2 v = cs(P->at)[i];
             ((float2*)(s_dyn + L.at))[i] = v;
-            if (OBJ)
-                ((float*)(s_dyn + L.dm))[i] = cs(P->dem)[i];
-            else
-                ((float*)(s_dyn + L.ln))[i] = __logf(v.x);
+            if (OBJ) ((float*)(s_dyn + L.dm))[i] = cs(P->dem)[i];
+            ((float2*)(s_dyn + L.nt))[i] = make_float2(OBJ ? P->u_top - v.x : -__logf(v.x), v.y);
         }
     const LS float* s_lat = MODE == SV_CLASS && K * N * R <= nlat ? (const LS float*)(s_dyn + L.lat) : nullptr;
     if (s_lat)
@@ -667,7 +675,7 @@ __global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, i
             at[q] = least(q, S.dy, BIN_ROW);
             r0[q] = r1[q] = INFINITY;
         }
-#pragma unroll 2
+#pragma unroll 4
         for (int j = 0; j < ry; ++j) {
             const float2 c = S.q3(2, j);
             const float e = OBJ ? S.d3(2, j) : S.e3(2, j).y;
@@ -694,23 +702,30 @@ __global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, i
             at[q] = least(q, S.dxy, BIN_BLK);
             r0[q] = r1[q] = INFINITY;
         }
-#pragma unroll 2
-        for (int i = 0; i < rx; ++i) {
-            const float2 c = S.q3(1, i);
-            const float e = OBJ ? S.d3(1, i) : S.e3(1, i).y;
+        auto fold_x = [&](auto&& bound) __attribute__((always_inline)) {
+#pragma unroll 4
+            for (int i = 0; i < rx; ++i) {
+                const float2 c = S.q3(1, i);
+                const float e = OBJ ? S.d3(1, i) : S.e3(1, i).y;
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const float p = at[q] + e;
-                if (OBJ) {
-                    const uint32_t o = S.off((p + S.dy) * BIN_ROW);
-                    r1[q] = fminf(r1[q], lower_by(tab(S.t_row, o), c.y));
-                    // x off y's paths: its own path bounds T
-                    r0[q] = fminf(r0[q], lower_by(tab(exy ? S.t_row : S.t_rowu, o), c.x));
-                } else {
-                    const float t = exy ? tab(S.t_row, S.off((p + S.dy) * BIN_ROW)) : div_threshold(tab(S.t_bin, S.off(p)), ray);
-                    r0[q] = fminf(r0[q], div_threshold(t, c.x));
-                }
+                for (int q = 0; q < Q; ++q) bound(q, at[q] + e, c);
             }
+        };
+        if (OBJ) {
+            const LS uint32_t* t_x = exy ? S.t_row : S.t_rowu;  // x off y's paths: its own path bounds T
+            fold_x([&](int q, float p, const float2& c) __attribute__((always_inline)) {
+                const uint32_t o = S.off((p + S.dy) * BIN_ROW);
+                r1[q] = fminf(r1[q], lower_by(tab(S.t_row, o), c.y));
+                r0[q] = fminf(r0[q], lower_by(tab(t_x, o), c.x));
+            });
+        } else if (exy) {
+            fold_x([&](int q, float p, const float2& c) __attribute__((always_inline)) {
+                r0[q] = fminf(r0[q], div_threshold(tab(S.t_row, S.off((p + S.dy) * BIN_ROW)), c.x));
+            });
+        } else {
+            fold_x([&](int q, float p, const float2& c) __attribute__((always_inline)) {
+                r0[q] = fminf(r0[q], div_threshold(div_threshold(tab(S.t_bin, S.off(p)), ray), c.x));
+            });
         }
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -724,30 +739,51 @@ __global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, i
             at[q] = least(q, S.dw, BIN_HEAD);
             r0[q] = r1[q] = r2[q] = INFINITY;
         }
-#pragma unroll 2
-        for (int i = 0; i < rw; ++i) {
-            const float2 c = S.q3(0, i);
-            const float e = OBJ ? S.d3(0, i) : S.e3(0, i).y;
+        // w's bound by what it feeds, the loop per case (a branch inside keeps the
+        // LDS reads of its iterations apart)
+        auto fold_w = [&](auto&& bound) __attribute__((always_inline)) {
+#pragma unroll 4
+            for (int i = 0; i < rw; ++i) {
+                const float2 c = S.q3(0, i);
+                const float e = OBJ ? S.d3(0, i) : S.e3(0, i).y;
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const float p = at[q] + e;
-                float t = -INFINITY;
-                if (OBJ) {
-                    const uint32_t o = S.off((p + S.dxy) * BIN_BLK);
-                    const float tx = tab(S.t_blk, o), ty = tab(S.t_blky, o);
-                    r1[q] = fminf(r1[q], lower_by(tx, c.y));
-                    r2[q] = fminf(r2[q], lower_by(ty, c.y));
-                    // w on a path to x or to y; a sink: no bound
-                    if (S.mx) t = fmaxf(t, lower_by(tx, c.x));
-                    if (S.my) t = fmaxf(t, lower_by(ty, c.x));
-                    r0[q] = fminf(r0[q], t);
-                } else {
-                    if (S.mx) t = fmaxf(t, tab(S.t_blk, S.off((p + S.dxy) * BIN_BLK)));
-                    if (S.my) t = fmaxf(t, div_threshold(tab(S.t_row, S.off((p + S.dy) * BIN_ROW)), rax));
-                    if (S.ms) t = fmaxf(t, div_threshold(div_threshold(tab(S.t_bin, S.off(p)), ray), rax));
-                    r0[q] = fminf(r0[q], div_threshold(t, c.x));
-                }
+                for (int q = 0; q < Q; ++q) bound(q, at[q] + e, c);
             }
+        };
+        if (OBJ) {
+            const bool mx = S.mx != 0, my = S.my != 0;
+            fold_w([&](int q, float p, const float2& c) __attribute__((always_inline)) {
+                const uint32_t o = S.off((p + S.dxy) * BIN_BLK);
+                const float tx = tab(S.t_blk, o), ty = tab(S.t_blky, o);
+                r1[q] = fminf(r1[q], lower_by(tx, c.y));
+                r2[q] = fminf(r2[q], lower_by(ty, c.y));
+                // w on a path to x or to y; a sink: no bound
+                r0[q] = fminf(r0[q], fmaxf(mx ? lower_by(tx, c.x) : -INFINITY, my ? lower_by(ty, c.x) : -INFINITY));
+            });
+        } else {
+            auto tx = [&](float p) __attribute__((always_inline)) { return tab(S.t_blk, S.off((p + S.dxy) * BIN_BLK)); };
+            auto ty = [&](float p) __attribute__((always_inline)) {
+                return div_threshold(tab(S.t_row, S.off((p + S.dy) * BIN_ROW)), rax);
+            };
+            if (S.mx && S.my)
+                fold_w([&](int q, float p, const float2& c) __attribute__((always_inline)) {
+                    r0[q] = fminf(r0[q], div_threshold(fmaxf(tx(p), ty(p)), c.x));
+                });
+            else if (S.mx)
+                fold_w([&](int q, float p, const float2& c) __attribute__((always_inline)) {
+                    r0[q] = fminf(r0[q], div_threshold(tx(p), c.x));
+                });
+            else if (S.my)
+                fold_w([&](int q, float p, const float2& c) __attribute__((always_inline)) {
+                    r0[q] = fminf(r0[q], div_threshold(ty(p), c.x));
+                });
+            else if (S.ms)
+                fold_w([&](int q, float p, const float2& c) __attribute__((always_inline)) {
+                    const float t = div_threshold(div_threshold(tab(S.t_bin, S.off(p)), ray), rax);
+                    r0[q] = fminf(r0[q], div_threshold(t, c.x));
+                });
+            else  // no such node
+                r0[0] = -INFINITY;
         }
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -779,7 +815,8 @@ __global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, i
             const uint32_t e = rq[i], slot = e >> 16;
             const int g = (int)(e >> 8 & 255u), ix = (int)(e & 255u);
             const SRow r = row_of<OBJ>(S, block_of<OBJ>(S, load_head(slot), g), ix);
-            plan_exact<MODE>(S, hx[slot] * (uint64_t)rw + (uint64_t)g, big, ix, r, (int)j, kk, seeds, ncand);
+            plan_exact<MODE>(S, hx[slot] * (uint64_t)rw + (uint64_t)g, big, ix, r, (int)j, kk, seeds, ncand,
+                             (LS Cand*)s_own);
         }
         __syncthreads();
         if (tid == 0) {
@@ -862,54 +899,67 @@ __global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, i
                                   (MODE == SV_CLASS ? 20.0f : 14.0f) * (float)q / (float)max(nl - 2, 1));
         const float mk = OBJ ? P->m32[sk] : 0.0f;
         LS float* f = (LS float*)(s_dyn + L.sc) + tid;
-        const LS float* ln = (const LS float*)(s_dyn + L.ln);
+        const LS float2* nt = (const LS float2*)(s_dyn + L.nt);
+        const bool whole = J->whole != 0;
         bool tl = true, th = true;  // the digits so far are those of the first (last) plan
         float c = OBJ ? 0.0f : 1.0f, cp = 0.0f, D = 0.0f;
+        const uint32_t sinks = P->sinks;
         for (int n = 0; n < N; ++n) {
             float w = lam * P->flow[n];
+            const int r = P->radix[n], e0 = n * R, lat = MODE == SV_CLASS ? sk * N * R + e0 : 0;
+            const uint32_t pm = P->pred[n];
             if (set > 0) {
                 const uint32_t hash = ((uint32_t)tid * 32u + (uint32_t)n + 1u) * 0x9E3779B1u;
-                w *= exp2f((float)(hash >> 8) * (3.0f * 0x1p-24f) - 1.5f);
+                w *= __builtin_amdgcn_exp2f((float)(hash >> 8) * (3.0f * 0x1p-24f) - 1.5f);
             }
-            const int r = P->radix[n], e0 = n * R, lat = MODE == SV_CLASS ? sk * N * R + e0 : 0;
-            int i0 = tl ? (int)s_b0[n] : 0, i1 = th ? (int)s_b1[n] : r - 1;
-            // away from both ends the following digits are free
-            if (tl && (v & 1) && i0 + (th ? 2 : 1) <= i1) {
-                ++i0;
-                i1 -= th ? 1 : 0;
+            // the cost w tau - ln a (objective: w tau + m_k d + u_max - u) is not
+            // negative, so its pattern orders as it does; the last eight bits
+            // carry the id, and the least key is the choice
+            uint32_t key = ~0u;
+            int i0 = 0, span = 255;  // ids i0 .. i0 + span
+            if (!whole) {
+                i0 = tl ? (int)s_b0[n] : 0;
+                int i1 = th ? (int)s_b1[n] : r - 1;
+                // away from both ends the following digits are free
+                if (tl && (v & 1) && i0 + (th ? 2 : 1) <= i1) {
+                    ++i0;
+                    i1 -= th ? 1 : 0;
+                }
+                span = i1 - i0;
             }
-            float best = -INFINITY;
-            int bi = i0;
             if (S.stg) {
+                const LS float2* q = nt + e0;
+                auto cost = [&](int i) __attribute__((always_inline)) {
+                    float y = fmaf(w, MODE == SV_CLASS ? class_lat(lat + i) : q[i].y, q[i].x);
+                    if (OBJ) y = fmaf(mk, S.s_dm[e0 + i], y);
+                    return (__float_as_uint(y) & 0x7fffff00u) | (uint32_t)i;
+                };
+                if (whole) {
 #pragma unroll 6
-                for (int i = 0; i < r; ++i) {
-                    const float t = MODE == SV_CLASS ? class_lat(lat + i) : ((const LS float*)S.s_at)[2 * (e0 + i) + 1];
-                    const float g = OBJ ? fmaf(-mk, S.s_dm[e0 + i], ((const LS float*)S.s_at)[2 * (e0 + i)]) : ln[e0 + i];
-                    const float y = fmaf(-w, t, g);
-                    const bool up = y > best && (uint32_t)(i - i0) <= (uint32_t)(i1 - i0);
-                    best = up ? y : best;
-                    bi = up ? i : bi;
+                    for (int i = 0; i < r; ++i) key = min(key, cost(i));
+                } else {
+#pragma unroll 6
+                    for (int i = 0; i < r; ++i)
+                        key = min(key, cost(i) | ((uint32_t)(i - i0) <= (uint32_t)span ? 0u : 0x80000000u));
                 }
             } else {
-                for (int i = i0; i <= i1; ++i) {
+                for (int i = i0; i <= min(i0 + span, r - 1); ++i) {
                     const float2 x = S.ent(e0 + i);
-                    const float t = MODE == SV_CLASS ? class_lat(lat + i) : x.y;
-                    const float y = fmaf(-w, t, OBJ ? fmaf(-mk, S.dem(e0 + i), x.x) : __logf(x.x));
-                    if (y > best) {
-                        best = y;
-                        bi = i;
-                    }
+                    float y = fmaf(w, MODE == SV_CLASS ? class_lat(lat + i) : x.y, OBJ ? P->u_top - x.x : -__logf(x.x));
+                    if (OBJ) y = fmaf(mk, S.dem(e0 + i), y);
+                    key = min(key, (__float_as_uint(y) & 0x7fffff00u) | (uint32_t)i);
                 }
             }
-            const float2 x = S.ent(e0 + bi);
-            const float t = MODE == SV_CLASS ? class_lat(lat + bi) : x.y;
-            tl = tl && bi == (int)s_b0[n];
-            th = th && bi == (int)s_b1[n];
+            tl = tl && (key & 255u) == (uint32_t)s_b0[n];
+            th = th && (key & 255u) == (uint32_t)s_b1[n];
+            const int e = e0 + (int)(key & 255u);
+            const float2 x = S.ent(e);
+            const float t = MODE == SV_CLASS ? class_lat(lat + (int)(key & 255u)) : x.y;
             c = OBJ ? c + x.x : c * x.x;
-            if (OBJ) D = D + S.dem(e0 + bi);
-            const float fn = t + col_max(f, P->pred[n]);
+            if (OBJ) D = D + S.dem(e);
+            const float fn = t + col_max(f, pm);
             f[n * WG] = fn;
-            if (P->sinks >> n & 1u) cp = fmaxf(cp, fn);
+            if (sinks >> n & 1u) cp = fmaxf(cp, fn);
         }
         // the fp32 values are the sweep's own (the same operations in node order)
         const float G = OBJ ? fmaf(S.nl, cp, c) : 0.0f;
@@ -1079,7 +1129,8 @@ __global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, i
             double x = 0.0, cp = 0.0, d = 0.0;
             if (tid < T && p < n) {
                 k = (int)(pairs[p] >> 27);
-                idx = J->cand[pairs[p] & 0x7ffffffu].index;
+                const uint32_t i = pairs[p] & 0x7ffffffu;
+                idx = nwg == 1 && i < (uint32_t)SOLVE_OWN ? s_own[i].index : J->cand[i].index;
                 decode64(P, idx, ids + tid, T);
                 pair_eval<OBJ>(P, ids + tid, f64 + tid, T, k, x, cp, d);
                 if (OBJ) {
@@ -1117,7 +1168,7 @@ __global__ void __launch_bounds__(WG) k_solve(const JobDev* __restrict__ jobs, i
         for (int k0 = 0; k0 < K; k0 += 4) {
             const uint32_t i = c0 + tid;
             if (i < nc) {
-                const Cand c = J->cand[i];
+                const Cand c = nwg == 1 && i < (uint32_t)SOLVE_OWN ? s_own[i] : J->cand[i];
                 for (int k = k0; k < min(K, k0 + 4); ++k) {
                     const bool in = OBJ ? fma(-P->m64[k], (double)c.cp, (double)c.corr) >= s_ct[k]
                                         : c.corr >= s_thr[k] && c.cp <= s_hi[k];
