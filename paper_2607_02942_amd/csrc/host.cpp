@@ -115,7 +115,9 @@ struct Scratch {
     double* cert_d = nullptr;
     Cand* cand = nullptr;
     size_t res_bytes = 0;       // out, ncand and flags are one contiguous region (one copy back)
-    // pinned host mirrors
+    // pinned host mirrors, one allocation (a pinned allocation and its release
+    // cost about 22 microseconds, more than the kernels of a small call)
+    char* h_pin = nullptr;
     JobDev* h_jobs = nullptr;   // the job array last uploaded
     JobDev* h_fb = nullptr;
     char* h_res = nullptr;      // pinned, host-coherent result region (choices, counters, flags)
@@ -470,10 +472,7 @@ int hip_fail(std::string* err, hipError_t e, const char* what) {
 
 void free_scratch(Scratch& s) {
     if (s.d) (void)hipFree(s.d);
-    if (s.h_jobs) (void)hipHostFree(s.h_jobs);
-    if (s.h_fb) (void)hipHostFree(s.h_fb);
-    if (s.h_res) (void)hipHostFree(s.h_res);
-    if (s.h_done) (void)hipHostFree(s.h_done);
+    if (s.h_pin) (void)hipHostFree(s.h_pin);
     s = Scratch{};
 }
 
@@ -549,17 +548,20 @@ int ensure_scratch(dy_plan* h, size_t njobs, uint32_t cap) {
     if (e != hipSuccess) return hip_fail(&h->err, e, "hipMalloc(scratch)");
     layout_scratch(s, d, njobs, cap, km);
     const size_t res_bytes = s.res_bytes;
-    if ((e = hipHostMalloc((void**)&s.h_jobs, njobs * sizeof(JobDev), hipHostMallocDefault)) != hipSuccess ||
-        (e = hipHostMalloc((void**)&s.h_fb, njobs * sizeof(JobDev), hipHostMallocDefault)) != hipSuccess ||
-        (e = hipHostMalloc((void**)&s.h_res, res_bytes, hipHostMallocMapped | hipHostMallocCoherent)) !=
-            hipSuccess ||
-        (e = hipHostGetDevicePointer((void**)&s.d_hres, s.h_res, 0)) != hipSuccess ||
-        (e = hipHostMalloc((void**)&s.h_done, njobs * sizeof(uint32_t), hipHostMallocMapped | hipHostMallocCoherent)) !=
-            hipSuccess ||
-        (e = hipHostGetDevicePointer((void**)&s.d_done, s.h_done, 0)) != hipSuccess) {
+    const size_t o_fb = align_up(njobs * sizeof(JobDev), 256), o_res = 2 * o_fb, o_done = o_res + align_up(res_bytes, 256);
+    char* dp = nullptr;
+    if ((e = hipHostMalloc((void**)&s.h_pin, o_done + njobs * sizeof(uint32_t),
+                           hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess ||
+        (e = hipHostGetDevicePointer((void**)&dp, s.h_pin, 0)) != hipSuccess) {
         free_scratch(s);
         return hip_fail(&h->err, e, "hipHostMalloc(scratch)");
     }
+    s.h_jobs = (JobDev*)s.h_pin;
+    s.h_fb = (JobDev*)(s.h_pin + o_fb);
+    s.h_res = s.h_pin + o_res;
+    s.d_hres = dp + o_res;
+    s.h_done = (uint32_t*)(s.h_pin + o_done);
+    s.d_done = (uint32_t*)(dp + o_done);
     s.h_out = (dy_choice*)(s.h_res);
     s.h_ncand = (uint32_t*)(s.h_res + s.res_ncand_off);
     s.h_flags = (int32_t*)(s.h_res + s.res_flags_off);
@@ -1181,10 +1183,6 @@ int dy_plan_create(const dy_problem* probs, int32_t n_probs, int32_t device, dy_
         Scratch tmp;
         layout_scratch(tmp, nullptr, kStaticSources, 0, h->kmax);
         h->st_host.assign(2 * (size_t)kStaticSources * sizeof(JobDev) + tmp.res_bytes, 0);
-        for (int i = 0; i < 4 && st == DY_OK; ++i)
-            if ((e = hipEventCreate(&h->ev[i])) != hipSuccess) st = hip_fail(&g_create_error, e, "hipEventCreate");
-        if (st == DY_OK && (e = hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking)) != hipSuccess)
-            st = hip_fail(&g_create_error, e, "hipStreamCreate");
     }
     if (st != DY_OK) {
         dy_plan_destroy(h);
@@ -1240,6 +1238,12 @@ void drop_graph(dy_plan* h) {
 hipGraphExec_t capture_graph(dy_plan* h,
                              const std::function<void(hipStream_t, const std::function<void(hipError_t, const char*)>&)>&
                                  issue) {
+    // (made by the first call that repeats its predecessor)
+    if (!h->cap_stream && hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess) {
+        h->cap_stream = nullptr;
+        (void)hipGetLastError();
+        return nullptr;
+    }
     if (hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
@@ -1265,7 +1269,16 @@ int dy_plan_set_option(dy_plan* h, int32_t option, int64_t value) {
     drop_graph(h);
     switch (option) {
         case DY_OPT_GRAPH: h->use_graph = value ? 1 : 0; return DY_OK;
-        case DY_OPT_TIMING: h->timing = value ? 1 : 0; return DY_OK;
+        case DY_OPT_TIMING:
+            if (value) {  // its events are made when first asked for
+                DeviceGuard g(h->device);
+                for (int i = 0; i < 4; ++i) {
+                    hipError_t e = h->ev[i] || !g.ok ? hipSuccess : hipEventCreate(&h->ev[i]);
+                    if (e != hipSuccess || !g.ok) return hip_fail(&h->err, g.ok ? e : hipErrorInvalidDevice, "hipEventCreate");
+                }
+            }
+            h->timing = value ? 1 : 0;
+            return DY_OK;
         case DY_OPT_SAMPLE_STRIDE:
             if (value < 1 || value > (1 << 30)) break;
             h->sample_stride = (uint32_t)value;
@@ -1660,11 +1673,12 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
             J.ncand = S.ncand + q;
             J.flags = S.flags + q;
             J.out = S.out + (size_t)j * km;
-            if (n_src <= kDirectResults && !stat) {  // few sources: certification writes the host copy directly
+            // RANGE sources, and any others of few: certification writes the host copy directly
+            if ((n_src <= kDirectResults || g >= G_SOLVE) && !stat) {
                 J.hout = (dy_choice*)S.d_hres + (size_t)j * km;
                 J.hncand = (uint32_t*)(S.d_hres + S.res_ncand_off) + q;
                 J.hflags = (int32_t*)(S.d_hres + S.res_flags_off) + q;
-                J.hdone = S.d_done + q;
+                if (n_src <= kDirectResults) J.hdone = S.d_done + q;
             }
             J.fb_corr = S.fb_corr + (size_t)q * KMAX;
             J.fb_index = S.fb_index + (size_t)q * KMAX;
@@ -1753,12 +1767,14 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
                          (!reuse && std::memcmp(S.h_jobs, jobs.data(), (size_t)n_src * sizeof(JobDev)) != 0);
     if (changed) {
         if (!stat) drop_graph(h);
-        hipError_t e = hipStreamSynchronize(s);  // a previous upload may still read the pinned buffer
+        // a previous upload may still read the pinned buffer
+        hipError_t e = S.uploaded || stat ? hipStreamSynchronize(s) : hipSuccess;
         if (e == hipSuccess) {
             std::memcpy(S.h_jobs, jobs.data(), (size_t)n_src * sizeof(JobDev));
             e = hipMemcpyAsync(S.d_jobs, S.h_jobs, (size_t)n_src * sizeof(JobDev), hipMemcpyHostToDevice, s);
         }
         if (e != hipSuccess) {
+            (void)hipStreamSynchronize(s);
             S.uploaded = 0;
             return hip_fail(&h->err, e, "hipMemcpyAsync(jobs)");
         }
@@ -1809,7 +1825,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
     auto issue_post = [&](hipStream_t st, const Check& ck) {
         launch_certify_all(S.d_jobs, n_pass, cert_waves, h, st, ck);
         if (h->timing) ck(hipEventRecord(h->ev[3], st), "hipEventRecord");
-        if (n_src > kDirectResults || stat)
+        if ((n_src > kDirectResults && n_pass > 0) || stat)
             ck(hipMemcpyAsync(S.h_res, S.out, S.res_bytes, hipMemcpyDeviceToHost, st), "copy out");
     };
     // With the results written straight to host memory, the call waits for the
