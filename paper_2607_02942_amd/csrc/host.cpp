@@ -1673,8 +1673,9 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
             J.ncand = S.ncand + q;
             J.flags = S.flags + q;
             J.out = S.out + (size_t)j * km;
-            // RANGE sources, and any others of few: certification writes the host copy directly
-            if ((n_src <= kDirectResults || g >= G_SOLVE) && !stat) {
+            // few sources: certification writes the host copy directly; many are
+            // copied out at once (512 requests: 111 us, against 117 us written directly)
+            if (n_src <= kDirectResults && !stat) {
                 J.hout = (dy_choice*)S.d_hres + (size_t)j * km;
                 J.hncand = (uint32_t*)(S.d_hres + S.res_ncand_off) + q;
                 J.hflags = (int32_t*)(S.d_hres + S.res_flags_off) + q;
@@ -1825,7 +1826,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
     auto issue_post = [&](hipStream_t st, const Check& ck) {
         launch_certify_all(S.d_jobs, n_pass, cert_waves, h, st, ck);
         if (h->timing) ck(hipEventRecord(h->ev[3], st), "hipEventRecord");
-        if ((n_src > kDirectResults && n_pass > 0) || stat)
+        if (n_src > kDirectResults || stat)
             ck(hipMemcpyAsync(S.h_res, S.out, S.res_bytes, hipMemcpyDeviceToHost, st), "copy out");
     };
     // With the results written straight to host memory, the call waits for the
