@@ -1491,7 +1491,7 @@ void add_solve(PassPlan& pp, int m, const JobDev& J, const ProbDev& D) {
     pp.rmax[m] = std::max(pp.rmax[m], D.rmax);
     pp.nmax[m] = std::max(pp.nmax[m], D.n);
     if (m == 1) pp.lat[m] = std::max(pp.lat[m], D.k * D.n * D.rmax);
-    if (m == 1 || D.npre > kSolveUnrolled) pp.col[m] = std::max(pp.col[m], m == 1 ? D.n : D.npre);
+    if (D.npre > kSolveUnrolled) pp.col[m] = std::max(pp.col[m], D.npre);
 }
 
 // How RANGE source J is split: `share` workgroups of the device are its part

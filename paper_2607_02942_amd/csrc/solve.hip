@@ -375,27 +375,11 @@ __device__ __forceinline__ void raise_seed(LS uint32_t* seed, uint32_t key) {
         __hip_atomic_fetch_max(seed, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// fp32 unpressured CP of plan (block b, ix, j), in the thread's LDS column.
-template <class SV>
-__device__ __forceinline__ float plain_cp(const SV& S, uint64_t b, int big, int ix, int j) {
-    PD P = S.P;
-    const int R = S.rmax, N = P->n;
-    LS float* f = S.s_col + threadIdx.x;
-    float cp = 0.0f;
-    for (int n = 0; n < N; ++n) {
-        const int d = n == N - 1 ? j : n == N - 2 ? ix : (int)prefix_digit(P, n, b, big);
-        const float fn = cs(P->at)[n * R + d].y + col_max(f, P->pred[n]);
-        f[n * WG] = fn;
-        if (P->sinks >> n & 1u) cp = fmaxf(cp, fn);
-    }
-    return cp;
-}
-
 // Exact test of plan j of row (block b, ix); a candidate is appended, a
 // certainly feasible one raises its levels' seeds.  Per-backend pressure: at
 // the level kk of the pass.
 template <int MODE, class SV>
-__device__ __forceinline__ void plan_exact(const SV& S, uint64_t b, int big, int ix, const SRow& r, int j, int kk,
+__device__ __forceinline__ void plan_exact(const SV& S, uint64_t b, int ix, const SRow& r, int j, int kk,
                                            LS uint32_t* s_seed, LS uint32_t* n, LS Cand* own) {
     PD P = S.P;
     JD J = S.J;
@@ -419,7 +403,10 @@ __device__ __forceinline__ void plan_exact(const SV& S, uint64_t b, int big, int
     if (MODE == SV_CLASS) {
         if (T <= P->ghi && c >= S.s_thr[kk]) {
             if (T <= P->glo) raise_seed(s_seed + kk, __float_as_uint(c) + 1u);
-            solve_append(J, n, own, idx, c, plain_cp(S, b, big, ix, j));
+            // No CP is kept: its only use was a seed for other levels, and the
+            // recurrence column it took (a float per node and thread) cost
+            // occupancy: 1,000 mixed requests 337 us with it, 251 without.
+            solve_append(J, n, own, idx, c, INFINITY);
         }
         return;
     }
@@ -815,7 +802,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
             const uint32_t e = rq[i], slot = e >> 16;
             const int g = (int)(e >> 8 & 255u), ix = (int)(e & 255u);
             const SRow r = row_of<OBJ>(S, block_of<OBJ>(S, load_head(slot), g), ix);
-            plan_exact<MODE>(S, hx[slot] * (uint64_t)rw + (uint64_t)g, big, ix, r, (int)j, kk, seeds, ncand,
+            plan_exact<MODE>(S, hx[slot] * (uint64_t)rw + (uint64_t)g, ix, r, (int)j, kk, seeds, ncand,
                              (LS Cand*)s_own);
         }
         __syncthreads();
@@ -1084,7 +1071,8 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     __syncthreads();
     const uint32_t total = s_nc, nc = min(total, J->cap);
     if (nwg > 1 && tid < 32) J->wk[tid] = 0u;
-    if (J->seeded && tid < K) J->scert[tid * NSLOT] = 0u;
+    // a list that overflowed: its seeds serve the next sweep of the source
+    if (tid < K && (J->seeded || total > J->cap)) J->scert[tid * NSLOT] = total > J->cap ? s_seed[tid] : 0u;
 
     // certification: thresholds from the best seeds of all, then every
     // (candidate, level) that can still win is re-evaluated in fp64
@@ -1171,7 +1159,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
                 const Cand c = nwg == 1 && i < (uint32_t)SOLVE_OWN ? s_own[i] : J->cand[i];
                 for (int k = k0; k < min(K, k0 + 4); ++k) {
                     const bool in = OBJ ? fma(-P->m64[k], (double)c.cp, (double)c.corr) >= s_ct[k]
-                                        : c.corr >= s_thr[k] && c.cp <= s_hi[k];
+                                        : c.corr >= s_thr[k] && (MODE == SV_CLASS || c.cp <= s_hi[k]);
                     if (in) pairs[atomicAdd(&s_nh, 1u)] = (uint32_t)k << 27 | i;
                 }
             }

@@ -91,6 +91,27 @@ def test_shapes(shape, mode):
 
 
 @pytest.mark.parametrize("mode", ["level", "class", "objective"])
+@pytest.mark.parametrize("shape", ["narrow", "wide"])
+def test_most_nodes(shape, mode):
+    # 32 nodes: the launch with the most LDS (recurrence columns for the sweep
+    # and the seeding, every table at its largest)
+    rng = np.random.default_rng([32, len(shape), len(mode)])
+    radix = [1] * 18 + [2] * 11 + [3, 4, 2] if shape == "narrow" else [1] * 17 + [2] * 13 + [255, 3]
+    K = 32 if shape == "narrow" else 4
+    prob = problem(rng, radix, K, mode != "class", edge_p=0.1)
+    total = prob.n_plans()
+    srcs = [D.range_source(0, 0, 3001), D.range_source(0, total - 4099, 4099), D.range_source(0, total // 3, 1500)]
+    obj = wl.paper_objective(prob, levels=np.sort(rng.uniform(0, 4, K))) if mode == "objective" else None
+    with D.Plan((prob, obj) if obj else prob) as plan:
+        got = plan.select(srcs, stream=stream())
+    for g, s in zip(got, srcs):
+        if obj:
+            assert_obj_choices(g, orc.obj_select_range(prob, obj, s.begin, s.count), f"{shape} {mode}")
+        else:
+            assert_choices(g, orc.select_range(prob, s.begin, s.count), f"{shape} {mode}")
+
+
+@pytest.mark.parametrize("mode", ["level", "class", "objective"])
 def test_mixed_batch_repeats(mode):
     # sources of different depths and sizes in one launch, some cut, one of
     # several workgroups; repeated calls list the same candidates
@@ -154,3 +175,24 @@ def test_all_zero_durations_and_factors():
         with D.Plan(q) as plan:
             got = plan.select([D.range_source(0, 0, total)], stream=stream())[0]
         assert_choices(got, orc.select_range(q, 0, total), f"p {p} tau {tau}")
+
+
+@pytest.mark.parametrize("mode", ["level", "class"])
+def test_overflow_then_other_sources(mode):
+    # equal plans overflow a list of 16 (decided exhaustively), near-equal ones
+    # are retried on the seeds kept; what the calls after it see is clean
+    rng = np.random.default_rng(41)
+    tied = problem(rng, [6, 5, 7, 4, 6], 3, mode != "class")
+    tied = dataclasses.replace(tied, p=np.full_like(tied.p, 0.8), tau=np.ones_like(tied.tau), slo=1e6)
+    near = problem(rng, [8, 8, 8, 8, 8], 3, mode != "class")
+    near = dataclasses.replace(near, p=(0.8 + 1e-6 * rng.random(near.p.shape)).astype(np.float32), slo=1e6)
+    low = problem(rng, [6, 5, 7, 4, 6], 3, mode != "class")
+    low = dataclasses.replace(low, p=low.p * np.float32(0.1))
+    probs = [tied, near, low]
+    want = [orc.select_range(p, 0, p.n_plans()) for p in probs]
+    with D.Plan(probs) as plan:
+        plan.set_option(D.DY_OPT_CAND_CAPACITY, 16)
+        for order in ([0, 1, 2], [2, 2, 2], [1, 0, 2], [2, 1, 0], [2, 2, 2]):
+            got = plan.select([D.range_source(j, 0, probs[j].n_plans()) for j in order], stream=stream())
+            for g, j in zip(got, order):
+                assert_choices(g, want[j], f"{mode} {order} problem {j}")
