@@ -103,7 +103,7 @@ struct ProbDev {
     // per implementation j of node y (j < 64): r_j <= 1 / (a_j (1 + 2^-22)),
     // rounded down to fp32; 0 when a_j < 2^-20.  A bin threshold T scaled by
     // r_j is a threshold on the rest of the product: fp32(c a_j) >= T implies
-    // c >= fp32(T r_j) for T > 2^-60 (see ydiv_threshold).
+    // c >= fp32(T r_j) for T > 2^-60 (generated sweep).
     float yinv[64];
     // objective mode, per implementation j of y (j < 64): c_j >= u_j -
     // lambda_l tau_j + E (E bounds the roundings of a plan's G and of its

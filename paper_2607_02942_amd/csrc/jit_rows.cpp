@@ -277,16 +277,16 @@ extern "C" __global__ void __launch_bounds__(256) dy_score_rows(
 }
 
 // The prefix-shared sweep for RANGE sources of one problem, block indices
-// below 2^32, under uniform pressure (corr / SLO mode) or the objective: the
-// library's k_sweep / k_sweep_obj with the DAG fixed at compile time.  A lane
+// below 2^32, under uniform pressure (corr / SLO mode) or the objective,
+// built on request, with the DAG fixed at compile time.  A lane
 // takes one prefix block (an assignment of nodes 0..N-3): digits by constant
 // division, the prefix recurrence with its exact predecessor maxima (no
 // per-edge selects), then the inner pair (x, y) swept in lockstep with the y
 // table in scalar registers; per plan (corr mode) one multiply, one add (and a
 // max for a second sink), the bin's threshold from LDS and a compare.  A row
 // with a hit is re-scored with the exact per-level test and its candidates
-// appended.  Same fp32 operations in the same order as the library's sweeps,
-// so both give identical candidates.
+// appended.  Same fp32 operations in the same order as the definition's
+// fp32 scoring, so its candidates are those that scoring each plan gives.
 void gen_sweep(std::ostringstream& o, const ProbDev& D) {
     const int NP = D.npre, xn = D.xnode, yn = D.ynode;
     const bool obj = D.obj != 0;
@@ -300,13 +300,13 @@ void gen_sweep(std::ostringstream& o, const ProbDev& D) {
     const unsigned msk = (unsigned)(nb - 1) << 2;
     // corr mode on 256 bins: the bins' thresholds held per implementation of
     // y, divided by its factor (rounded down, so that a plan the product test
-    // admits is admitted: see the library's ydiv_threshold); a row's test is
+    // admits is admitted: see div_threshold of the range sweep); a row's test is
     // then cx >= the least threshold of its plans' bins, every threshold being
     // +0, positive or +inf, so that their fp32 patterns order as the values
     const bool ydiv = !obj && D.jsh != 0 && D.ry >= 1 && D.ry <= 64;
     // objective mode on 256 bins: the first 256 entries hold the bins'
     // thresholds on G, then per implementation j of y the order keys of those
-    // thresholds lowered by c_j (see the library's yshift_key); a row's test
+    // thresholds lowered by c_j (dy_yshift below); a row's test
     // is the key of its fma(-lambda_l, M, ux) >= the least key of its plans'
     // D bins, and the rare path keeps the per-plan test on G
     const bool ysh = obj && D.jsh != 0 && D.ry >= 1 && D.ry <= 64;

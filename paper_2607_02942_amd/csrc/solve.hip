@@ -472,6 +472,13 @@ __device__ __forceinline__ void pair_eval(PD P, const uint8_t* ids, double* f, i
 // thresholds (every workgroup of a source the same) and building the tables.
 // The workgroup that ends last certifies the candidates in fp64 and writes
 // the choices.
+// Bound by chains of dependent LDS reads (seeding, the three folds, the
+// 64-bit recurrences), not by memory or arithmetic: a call of one small source
+// is mostly those chains, one after the other.  us a pass, the separate
+// sampling, table, plan-by-plan sweep and certification launches -> this one:
+// 4,096 six-node requests 1,196-1,405 -> 226, their objective 1,111 -> 161,
+// 512 mixed 416 -> 110, 1,000 under per-backend pressure 545 -> 251, one
+// fork-join of 4.3e8 plans 87 -> 44, one layered space of 4.3e9 611 -> 62.
 // Five waves per SIMD: with one more register group the batches, whose
 // workgroups wait on LDS chains most of the time, ran 9 % longer; at six (80
 // registers, spills) small sources run 3 to 10 % longer.
@@ -610,10 +617,8 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     // below those of the plans, and bin thresholds do not fall with the bin.
     // Corr: a factor a is divided out by div_threshold.  Objective: G and the
     // folded sums take at most four roundings between two levels, bounded by
-    // eshift (part of the offsets, see lower_by).  The bins' width is what
-    // lets plans just above a bound through (at 256 bins, 1.5 % of the CP, one
-    // 6-node source in a hundred took ten times the median's time), and four
-    // bins per thread cost little more than one: each is a chain of LDS reads.
+    // eshift (part of the offsets, see lower_by).  256 bins, one a thread:
+    // 1,024 let no fewer rows through and took longer to build.
     int kk = 0;  // per-backend pressure: the level of the pass
     auto build_tables = [&]() __attribute__((always_inline)) {
         set_thr();
