@@ -215,8 +215,10 @@ enum {
     DY_OPT_CAND_CAPACITY = 3,   /* candidate slots per source (default 1 << 16, min 16) */
     DY_OPT_FORCE_FP64 = 4,      /* 1: decide every level with the exhaustive fp64 path (default 0) */
     DY_OPT_JIT = 5,             /* kernels generated for the problem (hiprtc): 0 never; 1 (default) for
-                                   rows, and per-plan scores of rows; 2 as 1 and for the sweep of 32-bit
-                                   RANGE sources in plans of at most 8 problems */
+                                   rows, per-plan scores of rows, and the sweep of 32-bit RANGE sources
+                                   of at least 2^24 plans and 8 levels under per-backend pressure; 2 as
+                                   1 and for the sweep of every 32-bit RANGE source (sweeps: in plans
+                                   of at most 8 problems) */
     DY_OPT_GRAPH = 6,           /* 1: replay a call that repeats the previous one (same sources) from a
                                    HIP graph of its launches (default 1; calls with DY_OPT_TIMING on
                                    launch directly); results are identical */

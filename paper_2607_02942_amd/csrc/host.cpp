@@ -1551,6 +1551,8 @@ bool jit_ready(dy_plan* h, int p) {
 }  // namespace
 
 // The group of a RANGE source of problem H.
+constexpr int kGenLevels = 8;                // a generated sweep by default: levels and plans of the source at least
+constexpr uint64_t kGenPlans = 1ull << 24;   // (a compilation of about 0.4 s on first use)
 static int solve_group(const HostProb& H) { return G_SOLVE + (H.obj ? 2 : H.uniform ? 0 : 1); }
 
 // First share of a ROWS job scored in two shares (0: one pass).
@@ -1624,15 +1626,24 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
             else
                 grp[j] = G_GENERIC;
         }
-        // DY_OPT_JIT 2: RANGE sources of 32-bit plan indices run the sweep
-        // generated for their DAG, when the plan has few problems (one
-        // compilation each) and it compiles
-        if (h->use_jit >= 2 && !h->force_fp64 && h->hp.size() <= 8)
+        // RANGE sources of 32-bit plan indices run the sweep generated for
+        // their DAG, when the plan has few problems (one compilation each) and
+        // it compiles: all of them with DY_OPT_JIT 2, by default the large ones
+        // under per-backend pressure of many levels.  The library's sweep takes
+        // a pass per level there, the generated one a single pass; us a call,
+        // library and generated: 16 levels 403 / 203 (6.4e8 plans), 8 levels
+        // 338 / 121 (2.4e8), 308 / 221 (1.1e9), 172 / 141 (2.4e8); with levels
+        // less spread the library gained (75 / 99, 170 / 215), which sizes do
+        // not tell.  4 levels: 125 / 189 (1.1e9), 68 / 104 (4.3e8); one
+        // pressure on all backends, 16 levels: 74 / 197; objective 67 / 232.
+        if (h->use_jit >= 1 && !h->force_fp64 && h->hp.size() <= 8)
             for (int j = 0; j < n_src; ++j) {
                 const int p = src[j].problem;
                 const HostProb& H = h->hp[p];
-                if (src[j].kind == DY_SOURCE_RANGE && src[j].begin + src[j].count - 1 <= 0xffffffffull && jit_use(p) &&
-                    h->jit[p].sweep)
+                const bool gen = h->use_jit >= 2 ||
+                                 (!H.obj && !H.uniform && H.k >= kGenLevels && src[j].count >= kGenPlans);
+                if (src[j].kind == DY_SOURCE_RANGE && gen && src[j].begin + src[j].count - 1 <= 0xffffffffull &&
+                    jit_use(p) && h->jit[p].sweep)
                     grp[j] = H.obj ? (H.has_s2 ? G_OSWEEP_S2 : G_OSWEEP) : (H.has_s2 ? G_SWEEP_S2 : G_SWEEP);
             }
         // local-search seeds (DY_OPT_CLIMB 2: whole-space RANGE sources of

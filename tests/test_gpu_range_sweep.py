@@ -196,3 +196,18 @@ def test_overflow_then_other_sources(mode):
             got = plan.select([D.range_source(j, 0, probs[j].n_plans()) for j in order], stream=stream())
             for g, j in zip(got, order):
                 assert_choices(g, want[j], f"{mode} {order} problem {j}")
+
+
+@pytest.mark.parametrize("levels,count,generated", [(8, 1 << 24, 1), (8, (1 << 24) - 1, 0), (7, 1 << 24, 0)])
+def test_generated_for_many_class_levels(levels, count, generated):
+    # the route at the edges of its rule, against the library's sweep (exact choices)
+    prob = wl.per_class(dataclasses.replace(problem(np.random.default_rng(8), [12] * 7, levels, True)), (1.0, 0.5))
+    src = [D.range_source(0, 12345, count)]
+    got = []
+    for jit in (1, 0):
+        with D.Plan(prob) as plan:
+            plan.set_option(D.DY_OPT_JIT, jit)
+            got.append([plan.select(src, stream=stream())[0] for _ in range(3)])
+            assert plan.stats().generated_jobs == (generated if jit else 0)
+    for g in got[0] + got[1]:
+        assert repr(g) == repr(got[1][0])  # (NaN where infeasible)
