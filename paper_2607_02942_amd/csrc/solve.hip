@@ -1076,8 +1076,15 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     __syncthreads();
     const uint32_t total = s_nc, nc = min(total, J->cap);
     if (nwg > 1 && tid < 32) J->wk[tid] = 0u;
-    // a list that overflowed: its seeds serve the next sweep of the source
-    if (tid < K && (J->seeded || total > J->cap)) J->scert[tid * NSLOT] = total > J->cap ? s_seed[tid] : 0u;
+    // a list that overflowed: its seeds serve the next sweep of the source.  A
+    // source that was given seeds leaves every slot clear (a generated sweep,
+    // whose overflow this launch recovers, has sampled into all of them): the
+    // next call may give the job slot to another source without clearing it.
+    if (total > J->cap) {
+        if (tid < K) J->scert[tid * NSLOT] = s_seed[tid];
+    } else if (J->seeded) {
+        for (int i = tid; i < KMAX * NSLOT; i += WG) J->scert[i] = 0u;
+    }
 
     // certification: thresholds from the best seeds of all, then every
     // (candidate, level) that can still win is re-evaluated in fp64

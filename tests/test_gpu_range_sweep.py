@@ -211,3 +211,31 @@ def test_generated_for_many_class_levels(levels, count, generated):
             assert plan.stats().generated_jobs == (generated if jit else 0)
     for g in got[0] + got[1]:
         assert repr(g) == repr(got[1][0])  # (NaN where infeasible)
+
+
+def test_recovered_overflow_of_a_generated_sweep_leaves_no_seeds():
+    # a generated sweep samples into every seed slot; its list overflows and the
+    # library's sweep recovers it.  The next source in the same job slot has
+    # lower factors: a seed left behind would shut out all of its plans
+    rng = np.random.default_rng(23)
+    high = problem(rng, [12] * 6, 3, True)
+    low = dataclasses.replace(high, p=high.p * np.float32(0.1))
+    total = high.n_plans()
+    want_high, want_low = orc.select_range(high, 0, total), orc.select_range(low, 0, total)
+    rows = np.stack([rng.integers(0, 12, 20000) for _ in range(6)], axis=1).astype(np.uint8)
+    want_rows = orc.select_rows(low, rows)
+    d = torch.from_numpy(rows).cuda()
+    with D.Plan([high, low]) as plan:
+        plan.set_option(D.DY_OPT_JIT, 2)
+        whole = [D.range_source(j, 0, total) for j in range(2)]
+        plan.select([whole[0]], stream=stream())
+        assert plan.stats().generated_jobs == 1 and plan.stats().candidates > 16  # overflows a list of 16
+        plan.set_option(D.DY_OPT_CAND_CAPACITY, 16)
+        for jit, src, want in ((2, whole[1], want_low), (2, D.rows_source(1, d, 20000, 6), want_rows),
+                               (0, D.rows_source(1, d, 20000, 6), want_rows), (0, whole[1], want_low)):
+            plan.set_option(D.DY_OPT_JIT, 2)
+            assert_choices(plan.select([whole[0]], stream=stream())[0], want_high, "recovered")
+            st = plan.stats()
+            assert st.generated_jobs == 1 and st.fallbacks == 0 and st.candidates <= 16
+            plan.set_option(D.DY_OPT_JIT, jit)
+            assert_choices(plan.select([src], stream=stream())[0], want, f"after it, jit {jit} kind {src.kind}")
