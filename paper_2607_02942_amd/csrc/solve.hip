@@ -353,10 +353,18 @@ __device__ __forceinline__ bool row_test(const SV& S, const SRow& r) {
 }
 
 // Append to the source's candidate list: the workgroup's count is n (LDS), the
-// source's, where it has several, in device memory.
+// source's, where it has several, in device memory.  A list that overflowed
+// takes no more: a source may have 2^40 candidates, and a count of them all
+// would wrap.  (Past the capacity, at most 2^26, come at most the threads that
+// had found room: one a thread of the source's at most 2^10 workgroups.)
 __device__ __forceinline__ void solve_append(JD J, LS uint32_t* n, LS Cand* own, uint64_t index, float c, float cp) {
+    if (*(volatile LS uint32_t*)n > J->cap) return;
     uint32_t slot = __hip_atomic_fetch_add(n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (J->nwg > 1) slot = atomicAdd(J->wk, 1u);
+    if (J->nwg > 1) {
+        slot = atomicAdd(J->wk, 1u);
+        if (slot >= J->cap)
+            __hip_atomic_fetch_max(n, J->cap + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
     if (slot < (uint32_t)SOLVE_OWN) {  // (read back from here by a source's only workgroup)
         own[slot].index = index;
         own[slot].corr = c;

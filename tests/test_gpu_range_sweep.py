@@ -239,3 +239,15 @@ def test_recovered_overflow_of_a_generated_sweep_leaves_no_seeds():
             assert st.generated_jobs == 1 and st.fallbacks == 0 and st.candidates <= 16
             plan.set_option(D.DY_OPT_JIT, jit)
             assert_choices(plan.select([src], stream=stream())[0], want, f"after it, jit {jit} kind {src.kind}")
+
+
+def test_candidates_beyond_32_bits():
+    # 2^32 plans, every one a candidate: a 32-bit count of them is 0 again
+    n = 8
+    prob = problem(np.random.default_rng(2), [16] * n, 1, True)
+    prob = dataclasses.replace(prob, w=np.zeros(n, np.float32), slo=1e9)
+    assert prob.n_plans() == 1 << 32
+    with D.Plan(prob) as plan:
+        got = plan.select([D.range_source(0, 0, 1 << 32)], stream=stream())[0]
+        assert plan.stats().fallbacks == 1
+    assert_choices(got, orc.select_range(prob, 0, 1), "equal plans: the first is chosen")
