@@ -8,6 +8,7 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <deque>
 #include <functional>
 #include <new>
 #include <string>
@@ -701,9 +702,42 @@ void stage_objective(const dy_problem& pb, ProbDev& D, float2* at, float2* atx, 
     }
 }
 
+// A problem whose tables have their largest radix as row stride.  The caller's
+// stride may be up to 65536 for radices of at most 255; the kernels stage rows
+// in LDS and index the tables by the stride, so what is staged has none to spare.
+struct Packed {
+    dy_problem pb;
+    dy_objective obj;
+    std::vector<float> p, tau, size, cost;
+    std::vector<int32_t> backend;
+    explicit Packed(const dy_problem& from) : pb(from) {
+        const int N = pb.n_nodes, S = pb.max_radix, R = *std::max_element(pb.radix, pb.radix + N);
+        if (R == S) return;
+        auto rows = [&](auto& to, auto*& t) {
+            to.resize((size_t)N * R);
+            for (int n = 0; n < N; ++n) std::copy_n(t + (size_t)n * S, R, to.begin() + (size_t)n * R);
+            t = to.data();
+        };
+        rows(p, pb.p);
+        rows(tau, pb.tau);
+        pb.max_radix = R;
+        if (pb.objective) {  // (size and backend are not read)
+            obj = *pb.objective;
+            rows(cost, obj.cost);
+            pb.objective = &obj;
+        } else {
+            rows(size, pb.size);
+            rows(backend, pb.backend);
+        }
+    }
+    Packed(const Packed&) = delete;
+};
+
 // dry: derive the descriptors and tables on the host only (no HIP call); the
 // descriptors' table pointers then point into a host image that is discarded.
-int stage_problems(dy_plan* h, const dy_problem* probs, int32_t n_probs, std::string* err, bool dry = false) {
+int stage_problems(dy_plan* h, const dy_problem* given, int32_t n_probs, std::string* err, bool dry = false) {
+    std::deque<Packed> probs;
+    for (int j = 0; j < n_probs; ++j) probs.emplace_back(given[j]);
     struct Layout {
         size_t at, atx, dz, dem, lat, a64, lat64, dem64;
     };
@@ -719,7 +753,7 @@ int stage_problems(dy_plan* h, const dy_problem* probs, int32_t n_probs, std::st
     h->nmax = 0;
     h->nrmax = 0;
     for (int j = 0; j < n_probs; ++j) {
-        const dy_problem& pb = probs[j];
+        const dy_problem& pb = probs[j].pb;
         const size_t NR = (size_t)pb.n_nodes * pb.max_radix;
         // objective mode: one latency level (nominal durations)
         const int KL = pb.objective ? 1 : pb.n_levels;
@@ -748,7 +782,7 @@ int stage_problems(dy_plan* h, const dy_problem* probs, int32_t n_probs, std::st
     }
     ProbDev* descs = (ProbDev*)img.data();
     for (int j = 0; j < n_probs; ++j) {
-        const dy_problem& pb = probs[j];
+        const dy_problem& pb = probs[j].pb;
         const Layout& L = lay[j];
         const bool obj = pb.objective != nullptr;
         const int N = pb.n_nodes, R = pb.max_radix;

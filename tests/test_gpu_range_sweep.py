@@ -251,3 +251,29 @@ def test_candidates_beyond_32_bits():
         got = plan.select([D.range_source(0, 0, 1 << 32)], stream=stream())[0]
         assert plan.stats().fallbacks == 1
     assert_choices(got, orc.select_range(prob, 0, 1), "equal plans: the first is chosen")
+
+
+@pytest.mark.parametrize("mode", ["level", "class", "objective"])
+@pytest.mark.parametrize("stride", [256, 4096, 65536])
+def test_padded_tables(stride, mode):
+    # the row stride of the tables may be far above the radices
+    rng = np.random.default_rng([stride, len(mode)])
+    plain = problem(rng, [6, 5, 7, 4, 3], 3, mode != "class")
+
+    def pad(a):
+        b = np.zeros((a.shape[0], stride), a.dtype)
+        b[:, :a.shape[1]] = a
+        return b
+    prob = dataclasses.replace(plain, p=pad(plain.p), tau=pad(plain.tau), size=pad(plain.size),
+                               backend=pad(plain.backend))
+    total = plain.n_plans()
+    objs = [wl.paper_objective(p) if mode == "objective" else None for p in (plain, prob)]
+    check, oracle = ((assert_obj_choices, lambda b, c: orc.obj_select_range(plain, objs[0], b, c))
+                     if mode == "objective" else (assert_choices, lambda b, c: orc.select_range(plain, b, c)))
+    items = [p if o is None else (p, o) for p, o in zip((plain, prob), objs)]
+    for probs in (items[1:], items):
+        srcs = [D.range_source(j, b, total - b) for j in range(len(probs)) for b in (0, 777)]
+        with D.Plan(probs) as plan:
+            got = plan.select(srcs, stream=stream())
+        for g, s in zip(got, srcs):
+            check(g, oracle(s.begin, s.count), f"{mode} stride {stride} [{s.begin}+{s.count}]")
