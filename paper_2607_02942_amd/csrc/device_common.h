@@ -97,6 +97,11 @@ __device__ __forceinline__ float obj_threshold(float s, double err2) {
     return sub_rd((double)s, err2);
 }
 
+// fp32 estimate of a plan's J_k.  The weight m may lie beyond fp32 where D is
+// small enough (+inf here): a plan of D = 0 has J_k = G, one of D > 0 an
+// estimate of -inf, which raises no seed.
+__device__ __forceinline__ float obj_estimate(float m, float D, float G) { return D > 0.0f ? fmaf(-m, D, G) : G; }
+
 // Prefilter bin threshold: an fp32 value <= thr + m D_low (exact), m >= 0.
 __device__ __forceinline__ float obj_bin_threshold(float thr, double m, float dlow) {
     if (thr == -INFINITY) return -INFINITY;

@@ -1688,6 +1688,9 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         // source where the constructed plans leave 25.
         auto climb_ok = [&](int j) {
             const HostProb& H = h->hp[src[j].problem];
+            const ProbDev& Dj = h->hdesc[src[j].problem];
+            for (int k = 0; k < H.k && H.obj; ++k)
+                if (!finite_f(Dj.m32[k])) return false;  // (the search weighs D by it)
             return !h->force_fp64 && H.n <= kClimbNodes && src[j].kind == DY_SOURCE_RANGE &&
                    src[j].begin == 0 && !H.plans_saturated && src[j].count == H.n_plans;
         };

@@ -1105,7 +1105,7 @@ __global__ void __launch_bounds__(WG) k_sample_generic(const JobDev* __restrict_
         const bool ok = live && !bad;
 #pragma unroll 1
         for (int k = 0; k < K; ++k) {
-            uint32_t e = ok ? fkey(fmaf(-P->m32[k], D, G)) : 0u;
+            uint32_t e = ok ? fkey(obj_estimate(P->m32[k], D, G)) : 0u;
             e = wave_max_u32(e);
             if ((threadIdx.x & 63) == 0 && e)
                 atomicMax(J->scert + k * NSLOT + ((blockIdx.x * (WG / 64) + (threadIdx.x >> 6)) % NSLOT), e);
@@ -1806,7 +1806,7 @@ __global__ void __launch_bounds__(WG) k_score(const JobDev job, uint64_t unit_of
         }
         if (P->obj) {  // corr = U, cp[k] = the fp32 estimate of J_k, demand = D, every level admissible
             const float G = fmaf(-P->lam_l, cp0, U);
-            put_cp([&](int k) { return out ? fmaf(-P->m32[k], d, G) : NAN; });
+            put_cp([&](int k) { return out ? obj_estimate(P->m32[k], d, G) : NAN; });
             if (live) {
                 if (corr) corr[t] = out ? U : NAN;
                 if (dem) dem[t] = out ? d : NAN;
@@ -2024,8 +2024,8 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t spa
                     if (pl >= lb) continue;
                     const float2 u = s_v[wbase + (int)pl];
                     const float4 c = *(const float4*)(s_mk + k);
-                    const float4 w = OBJ ? make_float4(fmaf(-c.x, u.y, u.x), fmaf(-c.y, u.y, u.x), fmaf(-c.z, u.y, u.x),
-                                                       fmaf(-c.w, u.y, u.x))
+                    const float4 w = OBJ ? make_float4(obj_estimate(c.x, u.y, u.x), obj_estimate(c.y, u.y, u.x),
+                                                       obj_estimate(c.z, u.y, u.x), obj_estimate(c.w, u.y, u.x))
                                          : make_float4(u.x * c.x, u.x * c.y, u.x * c.z, u.x * c.w);
                     *(float4*)(cpo + e0 + f) = w;
                 }
@@ -2035,7 +2035,7 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t spa
                     const uint32_t pl = (f * kinv) >> 20, k = f - pl * (uint32_t)K;
                     if (pl >= lb) continue;
                     const float2 u = s_v[wbase + (int)pl];
-                    cpo[e0 + f] = OBJ ? fmaf(-s_mk[k], u.y, u.x) : u.x * s_mk[k];
+                    cpo[e0 + f] = OBJ ? obj_estimate(s_mk[k], u.y, u.x) : u.x * s_mk[k];
                 }
             }
             __builtin_amdgcn_wave_barrier();  // s_v is rewritten by the next step

@@ -402,7 +402,7 @@ __device__ __forceinline__ void plan_exact(const SV& S, uint64_t b, int ix, cons
         for (int k = 0; k < P->k; ++k)
             if (fma(-P->m64[k], (double)D, (double)G) >= (double)S.s_thr[k]) {
                 cand = true;
-                raise_seed(s_seed + k, fkey(fmaf(-P->m32[k], D, G)));
+                raise_seed(s_seed + k, fkey(obj_estimate(P->m32[k], D, G)));
             }
         if (cand) solve_append(J, n, own, idx, G, D);
         return;
@@ -966,7 +966,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
         for (int k = 0; k < K; ++k) {
             uint32_t e = 0;
             if (OBJ)
-                e = fkey(fmaf(-P->m32[k], D, G));
+                e = fkey(obj_estimate(P->m32[k], D, G));
             else if (MODE == SV_CLASS ? k == sk && cp <= P->glo : cp <= s_lo[k])
                 e = __float_as_uint(c) + 1u;
             e = wave_max_u32(e);

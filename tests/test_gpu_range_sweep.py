@@ -19,7 +19,7 @@ from paper_2607_02942_amd import dyplan as D  # noqa: E402
 from paper_2607_02942_amd import workload as wl  # noqa: E402
 
 from test_gpu_objective import assert_obj_choices  # noqa: E402
-from test_gpu_parity import assert_choices, stream  # noqa: E402
+from test_gpu_parity import assert_choices, run_score, stream  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -277,3 +277,27 @@ def test_padded_tables(stride, mode):
             got = plan.select(srcs, stream=stream())
         for g, s in zip(got, srcs):
             check(g, oracle(s.begin, s.count), f"{mode} stride {stride} [{s.begin}+{s.count}]")
+
+
+def test_weights_beyond_fp32():
+    # durations of zero leave the weights lambda_ld L_k unbounded: at the last
+    # level the product exceeds the largest fp32, and J_k = U all the same
+    rng = np.random.default_rng(12)
+    prob = problem(rng, [6, 5, 7, 4], 1, True)
+    prob = dataclasses.replace(prob, tau=np.zeros_like(prob.tau))
+    obj = wl.paper_objective(prob, levels=(0.0, 1e10, 1e25), lambda_ld=1e20)
+    total = prob.n_plans()
+    srcs = [D.range_source(0, 0, total), D.range_source(0, 100, total - 100)]
+    with D.Plan((prob, obj)) as plan:
+        for climb in (1, 2):
+            plan.set_option(D.DY_OPT_CLIMB, climb)
+            got = plan.select(srcs, stream=stream())
+            for g, s in zip(got, srcs):
+                assert_obj_choices(g, orc.obj_select_range(prob, obj, s.begin, s.count), f"[{s.begin}+{s.count}]")
+        rows = rng.integers(0, [6, 5, 7, 4], (5000, 4)).astype(np.uint8)
+        d = torch.from_numpy(rows).cuda()
+        got = plan.select([D.rows_source(0, d, 5000, 4)], stream=stream())[0]
+        assert_obj_choices(got, orc.obj_select_rows(prob, obj, rows), "rows")
+        for src, n in ((srcs[1], total - 100), (D.rows_source(0, d, 5000, 4), 5000)):
+            u, j, _, _ = run_score(plan, src, n, 3)
+            assert (j == u[:, None]).all()  # J_k = U, exactly
