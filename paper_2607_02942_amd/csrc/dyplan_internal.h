@@ -136,6 +136,17 @@ struct ProbDev {
     double eshift;
 };
 
+// Passed by value with a launch of at most LAUNCH_SIZES sources: how many
+// workgroups (certification: levels) of the grid each has.  The last workgroup
+// of a source tells a waiting host that its results are there; the call returns
+// when all have, and the next call, on any stream, may write other descriptors.
+// A surplus workgroup of the grid may start after that: it must leave without
+// reading one.  (Launches of more sources are waited for to their end.)
+constexpr int LAUNCH_SIZES = 64;
+struct LaunchSizes {
+    uint32_t n[LAUNCH_SIZES];
+};
+
 struct Cand {
     uint64_t index;
     float corr;

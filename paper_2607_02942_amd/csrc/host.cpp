@@ -23,11 +23,12 @@ hipError_t launch_table(JobDev* d_jobs, int njobs, hipStream_t s);
 hipError_t launch_sample_sweep(const JobDev* d_jobs, int n, bool has_s2, bool obj, uint64_t max_samples,
                                int npre_max, int npre_c, int kmax, hipStream_t s);
 // (weak: a build of the host code alone links without it)
-hipError_t launch_solve(const JobDev* d_jobs, int n, int mode, int nwg, int ent, int rmax, int nmax, int lat,
-                        int col, hipStream_t s) __attribute__((weak));
+hipError_t launch_solve(const JobDev* d_jobs, const LaunchSizes& sz, int n, int mode, int nwg, int ent, int rmax,
+                        int nmax, int lat, int col, hipStream_t s) __attribute__((weak));
 hipError_t launch_sample_generic(const JobDev* d_jobs, int n, uint64_t max_samples, int ncol, hipStream_t s);
 hipError_t launch_scan(const JobDev* d_jobs, int n, uint64_t max_units, int ncol, hipStream_t s);
-hipError_t launch_certify(const JobDev* d_jobs, int njobs, int waves, int kmax, int nmax, int nrmax, hipStream_t s);
+hipError_t launch_certify(const JobDev* d_jobs, const LaunchSizes& sz, int njobs, int waves, int kmax, int nmax,
+                          int nrmax, hipStream_t s) __attribute__((weak));
 hipError_t launch_exhaust(const JobDev* d_jobs, int njobs, uint64_t max_units, hipStream_t s);
 hipError_t launch_reseed(const JobDev* d_jobs, int njobs, hipStream_t s);
 hipError_t launch_seed_cands(const JobDev* d_jobs, int njobs, int kmax, int nmax, hipStream_t s);
@@ -1500,6 +1501,14 @@ hipError_t launch_jit_sweep(const dy_plan* h, const JobDev& J, int p, hipStream_
     return hipSuccess;
 }
 
+// The sizes that travel with a launch of n sources (not read in a larger one).
+template <class F>
+LaunchSizes launch_sizes(const JobDev* hjobs, int n, F size) {
+    LaunchSizes z{};
+    for (int q = 0; q < n && n <= LAUNCH_SIZES; ++q) z.n[q] = (uint32_t)size(hjobs[q]);
+    return z;
+}
+
 // Main scoring pass of the generated sweeps, the generic group and the RANGE
 // sources that one launch takes from seeds to choices.
 void launch_main(const dy_plan* h, const JobDev* d, const JobDev* hjobs, const PassPlan& pp, hipStream_t s,
@@ -1512,10 +1521,12 @@ void launch_main(const dy_plan* h, const JobDev* d, const JobDev* hjobs, const P
                         pp.ncol, s),
             "scan");
     for (int m = 0; m < kSolveModes; ++m)
-        for (int c = 0; c < pp.n[G_SOLVE + m]; c += 65535)
-            chk(launch_solve(d + pp.before(G_SOLVE + m) + c, std::min(65535, pp.n[G_SOLVE + m] - c), m, pp.nwg[m],
+        for (int c = 0; c < pp.n[G_SOLVE + m]; c += 65535) {
+            const int q = pp.before(G_SOLVE + m) + c, n = std::min(65535, pp.n[G_SOLVE + m] - c);
+            chk(launch_solve(d + q, launch_sizes(hjobs + q, n, [](const JobDev& J) { return J.nwg; }), n, m, pp.nwg[m],
                              pp.ent[m], pp.rmax[m], pp.nmax[m], pp.lat[m], pp.col[m], s),
                 "solve");
+        }
 }
 
 // The launch bounds of RANGE source J (mode m) of a plan.
@@ -1547,10 +1558,13 @@ void split_source(JobDev& J, const ProbDev& D, uint64_t share) {
     J.nwg = (int32_t)std::min<uint64_t>(std::max<uint64_t>(share, 1), (J.units + WG * kSolveSteps - 1) / (WG * kSolveSteps));
 }
 
-void launch_certify_all(const JobDev* d, int ntot, int cert_waves, const dy_plan* h, hipStream_t s,
+void launch_certify_all(const JobDev* d, const JobDev* hjobs, int ntot, int cert_waves, const dy_plan* h, hipStream_t s,
                         const std::function<void(hipError_t, const char*)>& chk) {
-    for (int c = 0; c < ntot; c += 65535)
-        chk(launch_certify(d + c, std::min(65535, ntot - c), cert_waves, h->kmax, h->nmax, h->nrmax, s), "certify");
+    for (int c = 0; c < ntot; c += 65535) {
+        const int n = std::min(65535, ntot - c);
+        const LaunchSizes z = launch_sizes(hjobs + c, n, [&](const JobDev& J) { return h->hdesc[J.prob - h->d_probs].k; });
+        chk(launch_certify(d + c, z, n, cert_waves, h->kmax, h->nmax, h->nrmax, s), "certify");
+    }
 }
 
 // Per-plan scores of a ROWS source through problem p's generated kernel
@@ -1872,7 +1886,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         if (h->timing) ck(hipEventRecord(h->ev[2], st), "hipEventRecord");
     };
     auto issue_post = [&](hipStream_t st, const Check& ck) {
-        launch_certify_all(S.d_jobs, n_pass, cert_waves, h, st, ck);
+        launch_certify_all(S.d_jobs, jobs.data(), n_pass, cert_waves, h, st, ck);
         if (h->timing) ck(hipEventRecord(h->ev[3], st), "hipEventRecord");
         if (n_src > kDirectResults || stat)
             ck(hipMemcpyAsync(S.h_res, S.out, S.res_bytes, hipMemcpyDeviceToHost, st), "copy out");
@@ -2018,7 +2032,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
             launch_table_all(S.d_fb, rp.before(G_SOLVE), s, chk);
             launch_main(h, S.d_fb, re.data(), rp, s, chk);
             jit_pass(re.data(), rp.before(G_JIT), rp.n[G_JIT], false, s, chk);
-            launch_certify_all(S.d_fb, rp.before(G_SOLVE), cert_waves, h, s, chk);
+            launch_certify_all(S.d_fb, re.data(), rp.before(G_SOLVE), cert_waves, h, s, chk);
         }
         if (n_ex > 0) {
             exhausted = true;

@@ -1360,8 +1360,8 @@ __host__ __device__ constexpr size_t cert_slot_doubles(int tab_d, int nf, int ca
 // search blockIdx.x * 4 + wave in source-major order (nsearch in all), each
 // with its own LDS slot (a CU holds few one-wave blocks).
 template <bool PACK>
-__global__ void __launch_bounds__(256) k_certify(const JobDev* __restrict__ jobs, int tab_d, int nf, int cache,
-                                                 int nsearch, int kmax) {
+__global__ void __launch_bounds__(256) k_certify(const JobDev* __restrict__ jobs, const LaunchSizes sizes, int tab_d,
+                                                 int nf, int cache, int nsearch, int kmax) {
     extern __shared__ double s_dyn64[];
     const int slot = PACK ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
     double* s_tab = s_dyn64 + (size_t)slot * cert_slot_doubles(tab_d, nf, cache);
@@ -1376,6 +1376,7 @@ __global__ void __launch_bounds__(256) k_certify(const JobDev* __restrict__ jobs
         k = q % kmax;
         g = 0;
     }
+    if (!PACK && gridDim.y <= (unsigned)LAUNCH_SIZES && (unsigned)k >= sizes.n[ji]) return;
     JD J = cs(jobs + ji);
     PD P = cs(J->prob);
     if (g >= J->cert_waves || k >= P->k) return;
@@ -2400,7 +2401,8 @@ hipError_t launch_scan(const JobDev* d_jobs, int n, uint64_t max_units, int ncol
     return hipSuccess;
 }
 
-hipError_t launch_certify(const JobDev* d_jobs, int njobs, int waves, int kmax, int nmax, int nrmax, hipStream_t s) {
+hipError_t launch_certify(const JobDev* d_jobs, const LaunchSizes& sz, int njobs, int waves, int kmax, int nmax, int nrmax,
+                          hipStream_t s) {
     // LDS sized by the plan's largest DAG (a fixed 58 KB let two blocks share a CU)
     const int tab_d = 3 * nrmax * (int)sizeof(double) <= CERT_LDS_TABLES ? 3 * nrmax : 0;
     // one wave per (source, level): four to a block, CERT_PACK_CACHE
@@ -2410,13 +2412,13 @@ hipError_t launch_certify(const JobDev* d_jobs, int njobs, int waves, int kmax, 
     const size_t lds_p = 4 * cert_slot_doubles(tab_p, nmax, CERT_PACK_CACHE) * sizeof(double);
     if (waves == 1 && lds_p <= 65536) {
         const int nsearch = njobs * kmax;
-        hipLaunchKernelGGL(k_certify<true>, dim3((unsigned)((nsearch + 3) / 4)), dim3(256), lds_p, s, d_jobs, tab_p,
-                           nmax, CERT_PACK_CACHE, nsearch, kmax);
+        hipLaunchKernelGGL(k_certify<true>, dim3((unsigned)((nsearch + 3) / 4)), dim3(256), lds_p, s, d_jobs, sz,
+                           tab_p, nmax, CERT_PACK_CACHE, nsearch, kmax);
         return hipGetLastError();
     }
     const size_t lds = cert_slot_doubles(tab_d, nmax, CERT_CACHE) * sizeof(double);
-    hipLaunchKernelGGL(k_certify<false>, dim3(waves, njobs, kmax), dim3(64), lds, s, d_jobs, tab_d, nmax, CERT_CACHE,
-                       0, kmax);
+    hipLaunchKernelGGL(k_certify<false>, dim3(waves, njobs, kmax), dim3(64), lds, s, d_jobs, sz, tab_d, nmax,
+                       CERT_CACHE, 0, kmax);
     return hipGetLastError();
 }
 

@@ -491,8 +491,8 @@ __device__ __forceinline__ void pair_eval(PD P, const uint8_t* ids, double* f, i
 // workgroups wait on LDS chains most of the time, ran 9 % longer; at six (80
 // registers, spills) small sources run 3 to 10 % longer.
 template <int MODE>
-__global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs, int ent, int rmax_all, int nlat,
-                                              int ncol, int nf, int lds) {
+__global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs, const LaunchSizes sizes, int ent,
+                                              int rmax_all, int nlat, int ncol, int nf, int lds) {
     constexpr bool OBJ = MODE == SV_OBJ;
     constexpr int NB = OBJ ? SOLVE_BINS_OBJ : SOLVE_BINS, Q = NB / WG;
     extern __shared__ __attribute__((aligned(16))) char s_dyn[];
@@ -503,6 +503,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     __shared__ uint32_t s_cnt[WG / 64];
     __shared__ Cand s_own[SOLVE_OWN];
     __shared__ uint32_t s_nh, s_nb, s_nr, s_nc, s_flag, s_rows;
+    if (gridDim.y <= (unsigned)LAUNCH_SIZES && blockIdx.x >= sizes.n[blockIdx.y]) return;
     JD J = cs(jobs + blockIdx.y);
     PD P = cs(J->prob);
     const uint32_t nwg = (uint32_t)J->nwg;
@@ -1233,8 +1234,8 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
 // of the sources, rmax their largest R_max, nmax their most nodes, lat: the
 // most durations of all levels of one (per-backend pressure), col: the most
 // prefix nodes of a source that needs recurrence columns, 0 for none.
-hipError_t launch_solve(const JobDev* d_jobs, int n, int mode, int nwg, int ent, int rmax, int nmax, int lat, int col,
-                        hipStream_t s) {
+hipError_t launch_solve(const JobDev* d_jobs, const LaunchSizes& sz, int n, int mode, int nwg, int ent, int rmax,
+                        int nmax, int lat, int col, hipStream_t s) {
     if (n == 0) return hipSuccess;
     constexpr int kEntMax = 1024;
     const int e = std::min(ent, kEntMax);
@@ -1243,11 +1244,11 @@ hipError_t launch_solve(const JobDev* d_jobs, int n, int mode, int nwg, int ent,
     const int lds = std::max(L.total, SOLVE_PAIRS * 4 + nmax * 9 * 64);
     const dim3 grid((unsigned)nwg, (unsigned)n);
     if (mode == SV_OBJ)
-        hipLaunchKernelGGL(k_solve<SV_OBJ>, grid, dim3(WG), lds, s, d_jobs, e, rmax, nl, col, nmax, lds);
+        hipLaunchKernelGGL(k_solve<SV_OBJ>, grid, dim3(WG), lds, s, d_jobs, sz, e, rmax, nl, col, nmax, lds);
     else if (mode == SV_CLASS)
-        hipLaunchKernelGGL(k_solve<SV_CLASS>, grid, dim3(WG), lds, s, d_jobs, e, rmax, nl, col, nmax, lds);
+        hipLaunchKernelGGL(k_solve<SV_CLASS>, grid, dim3(WG), lds, s, d_jobs, sz, e, rmax, nl, col, nmax, lds);
     else
-        hipLaunchKernelGGL(k_solve<SV_LEVEL>, grid, dim3(WG), lds, s, d_jobs, e, rmax, nl, col, nmax, lds);
+        hipLaunchKernelGGL(k_solve<SV_LEVEL>, grid, dim3(WG), lds, s, d_jobs, sz, e, rmax, nl, col, nmax, lds);
     return hipGetLastError();
 }
 

@@ -301,3 +301,30 @@ def test_weights_beyond_fp32():
         for src, n in ((srcs[1], total - 100), (D.rows_source(0, d, 5000, 4), 5000)):
             u, j, _, _ = run_score(plan, src, n, 3)
             assert (j == u[:, None]).all()  # J_k = U, exactly
+
+
+@pytest.mark.parametrize("mode", ["level", "class", "objective"])
+def test_other_sources_on_another_stream(mode):
+    # calls of at most 64 sources return on the results' arrival, and the next
+    # call uploads other sources on another stream: the surplus workgroups of
+    # the first launch (sources of one workgroup beside one of many) must not
+    # take the second's descriptors for theirs
+    rng = np.random.default_rng([64, len(mode)])
+    big = problem(rng, [12] * 7, 2, mode != "class")
+    small = [problem(rng, [4, 3, 5], 5, mode != "class") for _ in range(40)]
+    probs = [big] + small
+    objs = [wl.paper_objective(p) for p in probs]
+    order = [list(range(41)), list(range(40, -1, -1))]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    with D.Plan(list(zip(probs, objs)) if mode == "objective" else probs) as plan:
+        first = {}
+        for call in range(60):
+            js = order[call % 2]
+            got = plan.select([D.range_source(j, 0, probs[j].n_plans()) for j in js], stream=streams[call % 2])
+            for j, g in zip(js, got):
+                assert repr(first.setdefault(j, g)) == repr(g), f"call {call} problem {j}"
+    for j in range(1, 41):
+        if mode == "objective":
+            assert_obj_choices(first[j], orc.obj_select_range(probs[j], objs[j], 0, 60), f"problem {j}")
+        else:
+            assert_choices(first[j], orc.select_range(probs[j], 0, 60), f"problem {j}")
