@@ -155,6 +155,13 @@ struct Cand {
 
 enum JobFlags : int32_t { JF_OVERFLOW = 1, JF_BAD_ROW = 2 };
 
+// Plans of a range that share their first digits with its first (end = 0) or
+// last plan: node n takes ids lo..hi, the nodes after it are free.
+constexpr int SEED_BOXES = 4;
+struct SeedBox {
+    uint8_t end, n, lo, hi;
+};
+
 // Per source, per call.
 struct JobDev {
     const ProbDev* prob;
@@ -196,6 +203,8 @@ struct JobDev {
     // holds a seed
     uint64_t ublk0;
     uint8_t dig0[NMAX], dig1[NMAX];  // digits of the first and last plan
+    int32_t nbox;             // the parts of the range that its constructed seeds lie in
+    SeedBox box[SEED_BOXES];
     uint32_t* wk;             // [SOLVE_WK]
     int32_t nwg;
     int32_t seeded;

@@ -1539,6 +1539,49 @@ void add_solve(PassPlan& pp, int m, const JobDev& J, const ProbDev& D) {
     if (D.npre > kSolveUnrolled) pp.col[m] = std::max(pp.col[m], D.npre);
 }
 
+// The parts of range J that its seeds are constructed in: the largest of the
+// subtrees it consists of (below the node where its first and last plan part,
+// the ids between theirs; below each later node, the ids after the first
+// plan's and before the last plan's).  Construction is free in each; over the
+// whole range it would walk into an end, where a few plans share the digits of
+// the first or last one (2^28 plans from 2^33 on of a 12^11 space: seeds far
+// below the optimum, the candidate list overflowed, 2,340 us; in the four
+// largest parts 50 us).
+void seed_boxes(JobDev& J, const ProbDev& D) {
+    const int N = D.n;
+    int s = 0;
+    while (s < N - 1 && J.dig0[s] == J.dig1[s]) ++s;
+    double place[DY_MAX_NODES];
+    bool from0 = true, to_end = true;  // the nodes after s: the first plan's ids are 0, the last one's the largest
+    place[N - 1] = 1.0;
+    for (int n = N - 1; n > 0; --n) place[n - 1] = place[n] * D.radix[n];
+    for (int n = s + 1; n < N; ++n) {
+        from0 = from0 && J.dig0[n] == 0;
+        to_end = to_end && J.dig1[n] == D.radix[n] - 1;
+    }
+    struct Part {
+        double plans;
+        SeedBox box;
+    } parts[2 * DY_MAX_NODES + 1];
+    int np = 0;
+    auto add = [&](int end, int n, int lo, int hi) {
+        if (lo <= hi) parts[np++] = {(hi - lo + 1) * place[n], {(uint8_t)end, (uint8_t)n, (uint8_t)lo, (uint8_t)hi}};
+    };
+    const bool last = s == N - 1;
+    add(0, s, J.dig0[s] + (from0 || last ? 0 : 1), J.dig1[s] - (to_end || last ? 0 : 1));
+    for (int n = s + 1; n < N; ++n) {
+        const int e = n == N - 1 ? 0 : 1;
+        if (!from0) add(0, n, J.dig0[n] + e, D.radix[n] - 1);
+        if (!to_end) add(1, n, 0, J.dig1[n] - e);
+    }
+    std::stable_sort(parts, parts + np, [](const Part& a, const Part& b) { return a.plans > b.plans; });
+    J.nbox = 0;
+    while (J.nbox < std::min(np, SEED_BOXES) && parts[J.nbox].plans * 64 >= parts[0].plans) {
+        J.box[J.nbox] = parts[J.nbox].box;
+        ++J.nbox;
+    }
+}
+
 // How RANGE source J is split: `share` workgroups of the device are its part
 // of the call (by its blocks); a workgroup takes several units per thread, so
 // that the first of them (a seeding step) pays.
@@ -1555,6 +1598,10 @@ void split_source(JobDev& J, const ProbDev& D, uint64_t share) {
         p0 /= r;
         p1 /= r;
     }
+    if (J.whole)
+        J.nbox = 1;  // (its digits are not bounded)
+    else
+        seed_boxes(J, D);
     J.nwg = (int32_t)std::min<uint64_t>(std::max<uint64_t>(share, 1), (J.units + WG * kSolveSteps - 1) / (WG * kSolveSteps));
 }
 

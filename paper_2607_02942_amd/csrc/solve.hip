@@ -500,6 +500,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     __shared__ float s_thr[KMAX], s_lo[KMAX], s_hi[KMAX];
     __shared__ uint32_t s_seed[KMAX];
     __shared__ uint8_t s_b0[NMAX], s_b1[NMAX];
+    __shared__ SeedBox s_box[SEED_BOXES];
     __shared__ uint32_t s_cnt[WG / 64];
     __shared__ Cand s_own[SOLVE_OWN];
     __shared__ uint32_t s_nh, s_nb, s_nr, s_nc, s_flag, s_rows;
@@ -594,6 +595,12 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     if (tid < N) {  // digits of the source's first and last plan
         s_b0[tid] = J->dig0[tid];
         s_b1[tid] = J->dig1[tid];
+    }
+    if (tid < SEED_BOXES) {
+        s_box[tid].end = J->box[tid].end;
+        s_box[tid].n = J->box[tid].n;
+        s_box[tid].lo = J->box[tid].lo;
+        s_box[tid].hi = J->box[tid].hi;
     }
     if (tid == 0) {
         s_nh = 0;
@@ -882,8 +889,8 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     // plans lie on or next to the front of corr against CP: on the recipes'
     // workloads the best of them is the level's optimum more often than not,
     // and 0 to 3 % below it otherwise (256 sampled rows of plans: 2 to 13 %).
-    // Digits stay between those of the first and the last plan of the source,
-    // so every constructed plan lies in it.
+    // A range that is not the whole space is constructed in by parts, whole
+    // subtrees of it (seed_boxes), which the sets of threads take in turn.
     {
         const int per = MODE == SV_LEVEL ? WG : WG / K;  // plans per level
         const int sk = MODE == SV_LEVEL ? 0 : min(tid / per, K - 1);
@@ -902,14 +909,16 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
         LS float* f = (LS float*)(s_dyn + L.sc) + tid;
         const LS float2* nt = (const LS float2*)(s_dyn + L.nt);
         const bool whole = J->whole != 0;
-        bool tl = true, th = true;  // the digits so far are those of the first (last) plan
+        const int nbox = J->nbox;
+        const SeedBox box = s_box[set % nbox];
+        const uint8_t* ends = box.end ? s_b1 : s_b0;
         float c = OBJ ? 0.0f : 1.0f, cp = 0.0f, D = 0.0f;
         const uint32_t sinks = P->sinks;
         for (int n = 0; n < N; ++n) {
             float w = lam * P->flow[n];
             const int r = P->radix[n], e0 = n * R, lat = MODE == SV_CLASS ? sk * N * R + e0 : 0;
             const uint32_t pm = P->pred[n];
-            if (set > 0) {
+            if (set >= nbox) {
                 const uint32_t hash = ((uint32_t)tid * 32u + (uint32_t)n + 1u) * 0x9E3779B1u;
                 w *= __builtin_amdgcn_exp2f((float)(hash >> 8) * (3.0f * 0x1p-24f) - 1.5f);
             }
@@ -918,15 +927,9 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
             // carry the id, and the least key is the choice
             uint32_t key = ~0u;
             int i0 = 0, span = 255;  // ids i0 .. i0 + span
-            if (!whole) {
-                i0 = tl ? (int)s_b0[n] : 0;
-                int i1 = th ? (int)s_b1[n] : r - 1;
-                // away from both ends the following digits are free
-                if (tl && (v & 1) && i0 + (th ? 2 : 1) <= i1) {
-                    ++i0;
-                    i1 -= th ? 1 : 0;
-                }
-                span = i1 - i0;
+            if (!whole && n <= (int)box.n) {
+                i0 = n < (int)box.n ? (int)ends[n] : (int)box.lo;
+                span = n < (int)box.n ? 0 : (int)box.hi - i0;
             }
             if (S.stg) {
                 const LS float2* q = nt + e0;
@@ -951,8 +954,6 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
                     key = min(key, (__float_as_uint(y) & 0x7fffff00u) | (uint32_t)i);
                 }
             }
-            tl = tl && (key & 255u) == (uint32_t)s_b0[n];
-            th = th && (key & 255u) == (uint32_t)s_b1[n];
             const int e = e0 + (int)(key & 255u);
             const float2 x = S.ent(e);
             const float t = MODE == SV_CLASS ? class_lat(lat + (int)(key & 255u)) : x.y;

@@ -328,3 +328,36 @@ def test_other_sources_on_another_stream(mode):
             assert_obj_choices(first[j], orc.obj_select_range(probs[j], objs[j], 0, 60), f"problem {j}")
         else:
             assert_choices(first[j], orc.select_range(probs[j], 0, 60), f"problem {j}")
+
+
+@pytest.mark.parametrize("mode", ["level", "class", "objective"])
+@pytest.mark.parametrize("radix", [[5], [3, 4], [3, 1, 4], [2, 3, 2, 3]])
+def test_every_range_of_a_space(radix, mode):
+    # seeds are constructed in parts of a range; one constructed outside it would
+    # shut out its plans
+    rng = np.random.default_rng([len(radix), len(mode), 3])
+    prob = problem(rng, radix, 3, mode != "class")
+    total = prob.n_plans()
+    obj = wl.paper_objective(prob) if mode == "objective" else None
+    srcs = [D.range_source(0, b, c) for b in range(total) for c in range(1, total - b + 1)]
+    with D.Plan((prob, obj) if obj else prob) as plan:
+        got = plan.select(srcs, stream=stream())
+    for g, s in zip(got, srcs):
+        if obj:
+            assert_obj_choices(g, orc.obj_select_range(prob, obj, s.begin, s.count), f"{radix} [{s.begin}+{s.count}]")
+        else:
+            assert_choices(g, orc.select_range(prob, s.begin, s.count), f"{radix} [{s.begin}+{s.count}]")
+
+
+@pytest.mark.parametrize("mode", ["level", "objective"])
+def test_seeds_of_a_range_that_ends_inside_the_space(mode):
+    # ranges whose first and last plan part at neighbouring ids: the seeds lie in
+    # the large parts below, not next to the ends (tens of thousands of candidates)
+    rng = np.random.default_rng(71)
+    prob = problem(rng, [12] * 11, 3, True)
+    obj = wl.paper_objective(prob) if mode == "objective" else None
+    with D.Plan((prob, obj) if obj else prob) as plan:
+        plan.set_option(D.DY_OPT_CAND_CAPACITY, 1 << 26)
+        for begin, count in ((1 << 33, 1 << 24), ((1 << 33) - 5, 1 << 20), (12 ** 9 - 40, 12 ** 7)):
+            plan.select([D.range_source(0, begin, count)], stream=stream())
+            assert plan.stats().candidates < 10000, (begin, count, plan.stats().candidates)
