@@ -44,14 +44,19 @@ constexpr int SOLVE_REBUILD = 512; // rows unfolded before the tables are rebuil
 constexpr int SOLVE_OWN = 32;      // candidates kept in LDS as well
 constexpr int SOLVE_LAT = 4096;    // per-backend pressure: durations of all levels kept in LDS for the seeding up to this many
 
+constexpr int SEED_LEVELS = 8;     // per-backend pressure: levels seeded at a time, at most
+constexpr int SEED_NEAR = 3;       // ... and levels on each side that a level's plans are tried at
+
+constexpr uint32_t CAND_LEVEL = 0x7fc00000u;  // per-backend pressure: a candidate's level, in place of its CP
+
 enum { SV_LEVEL = 0, SV_CLASS = 1, SV_OBJ = 2 };
 
 // Dynamic LDS, in bytes from its start.  The certification reuses all of it.
 struct SolveLds {
-    int at, dm, e3, q3, d3, col, sc, nt, lat, hx, hv, bq, rq, total;
+    int at, dm, e3, q3, d3, col, sc, nt, lat, id, hx, hv, bq, rq, total;
 };
 
-__host__ __device__ inline SolveLds solve_lds(int ent, int rmax, int nlat, int ncol, int nmax, bool obj) {
+__host__ __device__ inline SolveLds solve_lds(int ent, int rmax, int nlat, int ncol, int nmax, bool obj, bool cls) {
     SolveLds L;
     int o = 0;
     auto take = [&](int bytes) {
@@ -67,12 +72,14 @@ __host__ __device__ inline SolveLds solve_lds(int ent, int rmax, int nlat, int n
     L.col = take(ncol * WG * 4);         // recurrence columns
     L.sc = o;                            // seeding only, where the queues follow: a recurrence column per node,
     L.nt = o + nmax * WG * 4;            // every node's (-ln a, tau) (objective: (u_max - u, tau)),
-    L.lat = L.nt + ent * 8;              // and (per-backend pressure) the durations at every level
+    L.lat = L.nt + ent * 8;              // and (per-backend pressure) the durations at every level and an id
+    L.id = L.lat + nlat * 4;             // column per node
     L.hx = take(SOLVE_Q * 8);            // parked heads: index, then product, paths, (sum of d)
     L.hv = take(SOLVE_Q * 4 * (obj ? 6 : 5));
     L.bq = take(SOLVE_Q * 4);            // parked blocks: head slot, w
     L.rq = take(SOLVE_Q * 4);            // parked rows: head slot, w, x
-    if (o < L.lat + nlat * 4) o = L.lat + nlat * 4;
+    const int seeding = L.id + (cls ? nmax * WG : 0);
+    if (o < seeding) o = seeding;
     L.total = o;
     return L;
 }
@@ -414,7 +421,8 @@ __device__ __forceinline__ void plan_exact(const SV& S, uint64_t b, int ix, cons
             // No CP is kept: its only use was a seed for other levels, and the
             // recurrence column it took (a float per node and thread) cost
             // occupancy: 1,000 mixed requests 337 us with it, 251 without.
-            solve_append(J, n, own, idx, c, INFINITY);
+            // The level takes its place, as a NaN, which passes no test of a CP.
+            solve_append(J, n, own, idx, c, __uint_as_float(CAND_LEVEL | (uint32_t)kk));
         }
         return;
     }
@@ -513,7 +521,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     const int K = P->k, N = P->n, R = P->rmax, rx = P->rx, ry = P->ry, npre = P->npre;
     const int rw = npre > 0 ? P->radix[npre - 1] : 1;
     const int big = J->big;
-    const SolveLds L = solve_lds(ent, rmax_all, nlat, ncol, nf, OBJ);
+    const SolveLds L = solve_lds(ent, rmax_all, nlat, ncol, nf, OBJ, MODE == SV_CLASS);
 
     // ---- the source's tables in LDS
     SolveT<NB> S;
@@ -827,6 +835,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
                              (LS Cand*)s_own);
         }
         __syncthreads();
+        set_thr();
         if (tid == 0) {
             s_nr = 0;
             s_rows += n;
@@ -891,10 +900,15 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     // and 0 to 3 % below it otherwise (256 sampled rows of plans: 2 to 13 %).
     // A range that is not the whole space is constructed in by parts, whole
     // subtrees of it (seed_boxes), which the sets of threads take in turn.
-    {
-        const int per = MODE == SV_LEVEL ? WG : WG / K;  // plans per level
-        const int sk = MODE == SV_LEVEL ? 0 : min(tid / per, K - 1);
-        const int v = MODE == SV_LEVEL ? tid : tid - sk * per;
+    // Per-backend pressure: at most SEED_LEVELS levels share the threads (with
+    // all of 32 the 8 plans a level had were 2.7 % below its optimum in the
+    // mean, now 0.3 %), and a plan serves the levels about its own as well.
+    const int rounds = MODE == SV_CLASS ? (K + SEED_LEVELS - 1) / SEED_LEVELS : 1;
+    for (int rd = 0; rd < rounds; ++rd) {
+        const int lpr = MODE == SV_LEVEL ? 1 : (K + rounds - 1) / rounds, per = WG / lpr;  // levels, plans of each
+        const int gl = min(tid / per, lpr - 1);
+        const int sk = min(rd * lpr + gl, K - 1);
+        const int v = tid - gl * per;
         const int nl = OBJ ? 4 : (per >= 32 ? (MODE == SV_LEVEL ? 32 : 16) : per);  // values of lambda
         const int q = v % nl, set = v / nl;
         float lam;
@@ -908,9 +922,10 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
         const float mk = OBJ ? P->m32[sk] : 0.0f;
         LS float* f = (LS float*)(s_dyn + L.sc) + tid;
         const LS float2* nt = (const LS float2*)(s_dyn + L.nt);
+        LS uint8_t* ids = (LS uint8_t*)(s_dyn + L.id) + tid;
         const bool whole = J->whole != 0;
         const int nbox = J->nbox;
-        const SeedBox box = s_box[set % nbox];
+        const SeedBox box = s_box[(MODE == SV_CLASS ? set + sk : set) % nbox];  // (few sets a level)
         const uint8_t* ends = box.end ? s_b1 : s_b0;
         float c = OBJ ? 0.0f : 1.0f, cp = 0.0f, D = 0.0f;
         const uint32_t sinks = P->sinks;
@@ -919,7 +934,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
             const int r = P->radix[n], e0 = n * R, lat = MODE == SV_CLASS ? sk * N * R + e0 : 0;
             const uint32_t pm = P->pred[n];
             if (set >= nbox) {
-                const uint32_t hash = ((uint32_t)tid * 32u + (uint32_t)n + 1u) * 0x9E3779B1u;
+                const uint32_t hash = ((uint32_t)(rd * WG + tid) * 32u + (uint32_t)n + 1u) * 0x9E3779B1u;
                 w *= __builtin_amdgcn_exp2f((float)(hash >> 8) * (3.0f * 0x1p-24f) - 1.5f);
             }
             // the cost w tau - ln a (objective: w tau + m_k d + u_max - u) is not
@@ -962,27 +977,42 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
             const float fn = t + col_max(f, pm);
             f[n * WG] = fn;
             if (sinks >> n & 1u) cp = fmaxf(cp, fn);
+            if (MODE == SV_CLASS) ids[n * WG] = (uint8_t)key;
         }
         // the fp32 values are the sweep's own (the same operations in node order)
+        if (MODE == SV_CLASS) {  // at the level it was made for and at those about it
+            if (cp <= P->glo) raise_seed(seeds + sk, __float_as_uint(c) + 1u);
+            for (int k = max(sk - SEED_NEAR, 0); k <= min(sk + SEED_NEAR, K - 1); ++k) {
+                if (k == sk || *(volatile LS uint32_t*)(seeds + k) > __float_as_uint(c)) continue;
+                float cpk = 0.0f;
+                for (int n = 0; n < N; ++n) {
+                    const float fn = class_lat((k * N + n) * R + (int)ids[n * WG]) + col_max(f, P->pred[n]);
+                    f[n * WG] = fn;
+                    if (sinks >> n & 1u) cpk = fmaxf(cpk, fn);
+                }
+                if (cpk <= P->glo) raise_seed(seeds + k, __float_as_uint(c) + 1u);
+            }
+            continue;
+        }
         const float G = OBJ ? fmaf(S.nl, cp, c) : 0.0f;
         for (int k = 0; k < K; ++k) {
             uint32_t e = 0;
             if (OBJ)
                 e = fkey(obj_estimate(P->m32[k], D, G));
-            else if (MODE == SV_CLASS ? k == sk && cp <= P->glo : cp <= s_lo[k])
+            else if (cp <= s_lo[k])
                 e = __float_as_uint(c) + 1u;
             e = wave_max_u32(e);
             if (lane == 0 && e) atomicMax(s_seed + k, e);
         }
-        __syncthreads();
     }
+    __syncthreads();
 
     // ---- the sweep (per-backend pressure: of each level)
     const uint64_t units = J->units;
     const uint64_t threads = (uint64_t)nwg * WG;
     const uint64_t steps = (units + threads - 1) / threads;
     const uint64_t gid = (uint64_t)tid * nwg + blockIdx.x;
-    uint32_t swept = 0;
+    uint32_t swept = 0, skipped = 0;
     for (kk = 0; kk < (MODE == SV_CLASS ? K : 1); ++kk) {
         if (MODE == SV_CLASS) {
             // a level whose durations are nowhere below those of a level swept
@@ -997,6 +1027,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
                 m &= m - 1;
                 skip = skip || s_thr[j] <= s_thr[kk];
             }
+            if (skip) skipped |= 1u << kk;
             if (skip) continue;
             swept |= 1u << kk;
             // the level's durations in the tables, and its bins: [cplo, ghi]
@@ -1057,6 +1088,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
         // every workgroup's, so it publishes and fences nothing.
         if (s_nc) {
             if (tid < K && s_seed[tid]) atomicMax(J->scert + tid * NSLOT + 1, s_seed[tid]);
+            if (MODE == SV_CLASS && tid == 0) atomicOr(J->wk + 2, skipped);
             __threadfence();
         }
         __syncthreads();
@@ -1075,6 +1107,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
         if (last) {
             __threadfence();
             if (tid == 0) s_nc = __hip_atomic_load(J->wk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (MODE == SV_CLASS) skipped = __hip_atomic_load(J->wk + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (tid < K) {
                 uint32_t* slot = J->scert + tid * NSLOT + 1;
                 s_seed[tid] = max(s_seed[tid], __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -1174,6 +1207,13 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
         if (tid == 0) s_nh = 0;
         __syncthreads();
     };
+    // per-backend pressure: a level's candidates are those its own sweep has
+    // listed, or any sweep where some workgroup left the level's out (without
+    // it every candidate took part at every level of no higher threshold:
+    // 512 requests of 2^14 plans at 32 levels 857 us, with it 386)
+    auto pass = [&](const Cand& c, int k) __attribute__((always_inline)) {
+        return (__float_as_uint(c.cp) & 31u) == (uint32_t)k || (skipped >> k & 1u);
+    };
     for (uint32_t c0 = 0; c0 < nc; c0 += WG)
         for (int k0 = 0; k0 < K; k0 += 4) {
             const uint32_t i = c0 + tid;
@@ -1181,7 +1221,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
                 const Cand c = nwg == 1 && i < (uint32_t)SOLVE_OWN ? s_own[i] : J->cand[i];
                 for (int k = k0; k < min(K, k0 + 4); ++k) {
                     const bool in = OBJ ? fma(-P->m64[k], (double)c.cp, (double)c.corr) >= s_ct[k]
-                                        : c.corr >= s_thr[k] && (MODE == SV_CLASS || c.cp <= s_hi[k]);
+                                        : c.corr >= s_thr[k] && (MODE == SV_CLASS ? pass(c, k) : c.cp <= s_hi[k]);
                     if (in) pairs[atomicAdd(&s_nh, 1u)] = (uint32_t)k << 27 | i;
                 }
             }
@@ -1241,7 +1281,7 @@ hipError_t launch_solve(const JobDev* d_jobs, const LaunchSizes& sz, int n, int 
     constexpr int kEntMax = 1024;
     const int e = std::min(ent, kEntMax);
     const int nl = mode == SV_CLASS ? std::min(lat, SOLVE_LAT) : 0;
-    const SolveLds L = solve_lds(e, rmax, nl, col, nmax, mode == SV_OBJ);
+    const SolveLds L = solve_lds(e, rmax, nl, col, nmax, mode == SV_OBJ, mode == SV_CLASS);
     const int lds = std::max(L.total, SOLVE_PAIRS * 4 + nmax * 9 * 64);
     const dim3 grid((unsigned)nwg, (unsigned)n);
     if (mode == SV_OBJ)

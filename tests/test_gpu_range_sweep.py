@@ -361,3 +361,24 @@ def test_seeds_of_a_range_that_ends_inside_the_space(mode):
         for begin, count in ((1 << 33, 1 << 24), ((1 << 33) - 5, 1 << 20), (12 ** 9 - 40, 12 ** 7)):
             plan.select([D.range_source(0, begin, count)], stream=stream())
             assert plan.stats().candidates < 10000, (begin, count, plan.stats().candidates)
+
+
+@pytest.mark.parametrize("K", [9, 17, 32])
+@pytest.mark.parametrize("near", [0.0, 1e-4])
+def test_class_levels_that_share_candidates(K, near):
+    # levels seeded in several rounds; equal levels, whose sweeps are left out
+    # (their candidates are another level's), in spaces of several workgroups
+    rng = np.random.default_rng([K, int(near > 0)])
+    prob = problem(rng, [12] * 6, K, False)
+    rho = np.sort(rng.uniform(0.0, 0.9, K)).astype(np.float32)
+    rho[1::3] = rho[0::3][:len(rho[1::3])]
+    prob = dataclasses.replace(prob, rho=np.stack([rho, rho * np.float32(0.5)], axis=1))
+    if near:  # many plans about the best
+        prob = dataclasses.replace(prob, p=(0.8 + near * rng.random(prob.p.shape)).astype(np.float32))
+    total = prob.n_plans()
+    srcs = [D.range_source(0, 0, total), D.range_source(0, 100003, total - 200000)]
+    with D.Plan(prob) as plan:
+        for call in range(2):
+            got = plan.select(srcs, stream=stream())
+            for g, s in zip(got, srcs):
+                assert_choices(g, orc.select_range(prob, s.begin, s.count), f"K {K} [{s.begin}+{s.count}] call {call}")
