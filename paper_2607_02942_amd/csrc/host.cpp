@@ -1584,7 +1584,10 @@ void seed_boxes(JobDev& J, const ProbDev& D) {
 
 // How RANGE source J is split: `share` workgroups of the device are its part
 // of the call (by its blocks); a workgroup takes several units per thread, so
-// that the first of them (a seeding step) pays.
+// that the first of them (a seeding step) pays, or one where the device is not
+// full even so (up to a workgroup per CU; us a call, four units a thread / one:
+// 2^20 plans of 20 nodes 66 / 54, 12^7 plans at 8 per-backend levels 71 / 58;
+// past a workgroup per CU, 12^8 plans 39 / 43).
 void split_source(JobDev& J, const ProbDev& D, uint64_t share) {
     const uint64_t rw = D.npre > 0 ? (uint64_t)D.radix[D.npre - 1] : 1;
     J.ublk0 = J.blk_first / rw;
@@ -1602,7 +1605,8 @@ void split_source(JobDev& J, const ProbDev& D, uint64_t share) {
         J.nbox = 1;  // (its digits are not bounded)
     else
         seed_boxes(J, D);
-    J.nwg = (int32_t)std::min<uint64_t>(std::max<uint64_t>(share, 1), (J.units + WG * kSolveSteps - 1) / (WG * kSolveSteps));
+    const uint64_t several = (J.units + WG * kSolveSteps - 1) / (WG * kSolveSteps), one = (J.units + WG - 1) / WG;
+    J.nwg = (int32_t)std::min(std::max<uint64_t>(share, 1), std::max(several, std::min(one, share / kSolveWgs)));
 }
 
 void launch_certify_all(const JobDev* d, const JobDev* hjobs, int ntot, int cert_waves, const dy_plan* h, hipStream_t s,
