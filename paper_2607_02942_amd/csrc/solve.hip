@@ -835,7 +835,6 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
                              (LS Cand*)s_own);
         }
         __syncthreads();
-        set_thr();
         if (tid == 0) {
             s_nr = 0;
             s_rows += n;
@@ -877,7 +876,10 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
             __syncthreads();
             const bool any = s_nb > 0;
             __syncthreads();
-            if (any) drain_blocks();
+            if (any) {
+                drain_blocks();
+                set_thr();  // (here, not after each round of rows, whose make-up varies)
+            }
             if (s_rows > (uint32_t)SOLVE_REBUILD) {
                 __syncthreads();
                 if (tid == 0) s_rows = 0;
