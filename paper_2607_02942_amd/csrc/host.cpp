@@ -2045,19 +2045,24 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
     // those sources again (each round raises the thresholds); whatever still
     // overflows after kReseedRounds is decided exhaustively
     constexpr int kReseedRounds = 3;
+    std::vector<char> decided((any_flag & JF_OVERFLOW) ? (size_t)n_src : 0, 0);  // exhaustively
     for (int round = 0; round <= kReseedRounds && !h->force_fp64 && (any_flag & JF_OVERFLOW); ++round) {
         PassPlan rp;
         std::vector<JobDev> re, ex;
         uint64_t fb_units = 0;
         for (int g = 0; g < kGroups; ++g)
             for (int q = 0; q < n_src; ++q) {
-                if (!(S.h_flags[q] & JF_OVERFLOW)) continue;
+                if (!(S.h_flags[q] & JF_OVERFLOW) || decided[q]) continue;
                 const int j = order[q];
                 const HostProb& H = h->hp[src[j].problem];
                 // a generated sweep's source is rescored by the library
                 if ((grp[j] < kSweepGroups ? solve_group(H) : grp[j]) != g) continue;
                 JobDev J = jobs[q];
-                if (round < kReseedRounds) {
+                // the range sweep leaves each level's best seed of the whole source
+                // (per-backend pressure: of the levels it swept), so one more sweep
+                // has all it can gain
+                const int tries = grp[j] == G_SOLVE || grp[j] == G_SOLVE + 2 ? 1 : kReseedRounds;
+                if (round < tries) {
                     J.seeded = 1;
                     ++rp.n[g];
                     if (g < G_JIT) rp.units[g] = std::max(rp.units[g], J.units);
@@ -2069,6 +2074,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
                     stats.fallbacks += H.k;
                     fb_units = std::max(fb_units, J.count);
                     ex.push_back(J);
+                    decided[q] = 1;
                 }
             }
         const int n_re = (int)re.size(), n_ex = (int)ex.size();
@@ -2094,7 +2100,6 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         chk(hipMemcpyAsync(S.h_res, S.out, S.res_bytes, hipMemcpyDeviceToHost, s), "copy out");
         chk(hipStreamSynchronize(s), "hipStreamSynchronize");
         if (st != DY_OK) return st;
-        if (n_re == 0) break;
         stats.candidates = 0;
         for (int q = 0; q < n_src; ++q) stats.candidates += std::min<uint64_t>(S.h_ncand[q], cap);
     }

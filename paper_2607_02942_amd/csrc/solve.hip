@@ -1119,7 +1119,9 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     }
     if (!last) return;
     __syncthreads();
-    const uint32_t total = s_nc, nc = min(total, J->cap);
+    // (a list that overflowed decides nothing: the host sweeps again, or decides
+    // the source exhaustively; one workgroup certified 65,536 plans in 5 ms)
+    const uint32_t total = s_nc, nc = total > J->cap ? 0u : total;
     if (nwg > 1 && tid < 32) J->wk[tid] = 0u;
     // a list that overflowed: its seeds serve the next sweep of the source.  A
     // source that was given seeds leaves every slot clear (a generated sweep,

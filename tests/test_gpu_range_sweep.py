@@ -382,3 +382,25 @@ def test_class_levels_that_share_candidates(K, near):
             got = plan.select(srcs, stream=stream())
             for g, s in zip(got, srcs):
                 assert_choices(g, orc.select_range(prob, s.begin, s.count), f"K {K} [{s.begin}+{s.count}] call {call}")
+
+
+def test_overflows_of_every_kind_in_one_call():
+    # sources that end exhaustively after one more sweep (equal plans), after
+    # three (per-backend pressure, a generated sweep's), that are recovered, and
+    # that never overflow, in one call; each is decided once
+    rng = np.random.default_rng(77)
+    radix, probs = [6, 5, 7, 4, 6], []
+    for uniform in (True, False):
+        tied = problem(rng, radix, 3, uniform)
+        probs.append(dataclasses.replace(tied, p=np.full_like(tied.p, 0.8), tau=np.ones_like(tied.tau), slo=1e6))
+    probs += [dataclasses.replace(problem(rng, [8] * 5, 3, True), slo=1e6), problem(rng, [3, 2], 3, True)]
+    want = [orc.select_range(p, 0, p.n_plans()) for p in probs]
+    for jit in (0, 2):
+        with D.Plan(probs) as plan:
+            plan.set_option(D.DY_OPT_CAND_CAPACITY, 16)
+            plan.set_option(D.DY_OPT_JIT, jit)
+            for call in range(2):
+                got = plan.select([D.range_source(j, 0, p.n_plans()) for j, p in enumerate(probs)], stream=stream())
+                assert plan.stats().fallbacks == 6  # two sources of three levels
+                for g, w in zip(got, want):
+                    assert_choices(g, w, f"jit {jit} call {call}")
