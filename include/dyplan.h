@@ -216,9 +216,9 @@ enum {
     DY_OPT_FORCE_FP64 = 4,      /* 1: decide every level with the exhaustive fp64 path (default 0) */
     DY_OPT_JIT = 5,             /* kernels generated for the problem (hiprtc): 0 never; 1 (default) for
                                    rows, per-plan scores of rows, and the sweep of 32-bit RANGE sources
-                                   of at least 2^24 plans and 8 levels under per-backend pressure; 2 as
-                                   1 and for the sweep of every 32-bit RANGE source (sweeps: in plans
-                                   of at most 8 problems) */
+                                   of at least 2^24 plans whose last three nodes have few (4; 128 in
+                                   problems of 12 or more nodes); 2 as 1 and for the sweep of every
+                                   32-bit RANGE source (sweeps: in plans of at most 8 problems) */
     DY_OPT_GRAPH = 6,           /* 1: replay a call that repeats the previous one (same sources) from a
                                    HIP graph of its launches (default 1; calls with DY_OPT_TIMING on
                                    launch directly); results are identical */

@@ -1649,9 +1649,26 @@ bool jit_ready(dy_plan* h, int p) {
 
 }  // namespace
 
+constexpr uint64_t kGenPlans = 1ull << 24;   // a generated sweep by default: plans of the source at least
+constexpr int kGenFold = 4, kGenFoldDeep = 128;  // ... and of its last three nodes at most (see gen_pays)
+
+// The sweep generated for a problem's DAG is the better one where the library's
+// folds little: the library tests a head for the plans of the last three nodes,
+// the generated sweep each plan.  us a call, library / generated (a compilation
+// of about 0.4 s on first use), heads of seven nodes of 12 ids: last three nodes
+// of 1 plan 346 / 130 (per-backend pressure 681 / 142, objective 363 / 174), 2
+// plans 354 / 233, 4 plans 348 / 264, 12 plans 352 / 1,165.  Heads too long to be
+// unrolled cost ten times as much (20 nodes of 2 ids): 27 plans 128 / 54, 64
+// plans 128 / 61 (per-backend 152 / 107), 144 plans 132 / 142, 1,728 plans 134 /
+// 249.  Under per-backend pressure of 4 to 32 levels the library took 0.23 to
+// 1.1 of the generated sweep's time in 35 of 36 spaces of 2.5e7 to 2e9 plans.
+static bool gen_pays(const ProbDev& D) {
+    int64_t fold = 1;
+    for (int n = std::max(D.n - 3, 0); n < D.n; ++n) fold *= D.radix[n];
+    return fold <= (D.npre > kSolveUnrolled ? kGenFoldDeep : kGenFold);
+}
+
 // The group of a RANGE source of problem H.
-constexpr int kGenLevels = 8;                // a generated sweep by default: levels and plans of the source at least
-constexpr uint64_t kGenPlans = 1ull << 24;   // (a compilation of about 0.4 s on first use)
 static int solve_group(const HostProb& H) { return G_SOLVE + (H.obj ? 2 : H.uniform ? 0 : 1); }
 
 // First share of a ROWS job scored in two shares (0: one pass).
@@ -1727,20 +1744,13 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         }
         // RANGE sources of 32-bit plan indices run the sweep generated for
         // their DAG, when the plan has few problems (one compilation each) and
-        // it compiles: all of them with DY_OPT_JIT 2, by default the large ones
-        // under per-backend pressure of many levels.  The library's sweep takes
-        // a pass per level there, the generated one a single pass; us a call,
-        // library and generated: 16 levels 403 / 203 (6.4e8 plans), 8 levels
-        // 338 / 121 (2.4e8), 308 / 221 (1.1e9), 172 / 141 (2.4e8); with levels
-        // less spread the library gained (75 / 99, 170 / 215), which sizes do
-        // not tell.  4 levels: 125 / 189 (1.1e9), 68 / 104 (4.3e8); one
-        // pressure on all backends, 16 levels: 74 / 197; objective 67 / 232.
+        // it compiles: all of them with DY_OPT_JIT 2, by default large ones
+        // whose last three nodes have few plans
         if (h->use_jit >= 1 && !h->force_fp64 && h->hp.size() <= 8)
             for (int j = 0; j < n_src; ++j) {
                 const int p = src[j].problem;
                 const HostProb& H = h->hp[p];
-                const bool gen = h->use_jit >= 2 ||
-                                 (!H.obj && !H.uniform && H.k >= kGenLevels && src[j].count >= kGenPlans);
+                const bool gen = h->use_jit >= 2 || (src[j].count >= kGenPlans && gen_pays(h->hdesc[p]));
                 if (src[j].kind == DY_SOURCE_RANGE && gen && src[j].begin + src[j].count - 1 <= 0xffffffffull &&
                     jit_use(p) && h->jit[p].sweep)
                     grp[j] = H.obj ? (H.has_s2 ? G_OSWEEP_S2 : G_OSWEEP) : (H.has_s2 ? G_SWEEP_S2 : G_SWEEP);

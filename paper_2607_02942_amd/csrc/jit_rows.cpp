@@ -276,9 +276,9 @@ extern "C" __global__ void __launch_bounds__(256) dy_score_rows(
     o << "  }\n}\n";
 }
 
-// The prefix-shared sweep for RANGE sources of one problem, block indices
-// below 2^32, under uniform pressure (corr / SLO mode) or the objective,
-// built on request, with the DAG fixed at compile time.  A lane
+// The prefix-shared sweep for RANGE sources of one problem, plan indices below
+// 2^32, in each mode (by default for large sources whose last three nodes have
+// few plans), with the DAG fixed at compile time.  A lane
 // takes one prefix block (an assignment of nodes 0..N-3): digits by constant
 // division, the prefix recurrence with its exact predecessor maxima (no
 // per-edge selects), then the inner pair (x, y) swept in lockstep with the y

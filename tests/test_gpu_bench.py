@@ -1,6 +1,5 @@
-"""The benchmark's workloads whose main pass is a sweep generated for the DAG
-(large spaces under per-backend pressure): the run ends with its line, and the
-choices are the oracle's stored selections."""
+"""The benchmark's large spaces under per-backend pressure: the run ends with its
+line, and the choices are the oracle's stored selections."""
 import json
 import os
 import subprocess
@@ -23,4 +22,4 @@ def test_per_class_workloads(workload):
     assert res.returncode == 0, res.stderr[-2000:]
     line = json.loads([x for x in res.stdout.splitlines() if x.startswith("{")][-1])
     assert line["golden_check"].startswith("every choice equals")
-    assert line["roofline"]["kernel"] == "dy_sweep" and line["roofline"]["frac"] < 1
+    assert line["roofline"]["kernel"] in ("k_solve", "dy_sweep") and 0 < line["roofline"]["frac"] < 1

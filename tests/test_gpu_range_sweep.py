@@ -198,14 +198,18 @@ def test_overflow_then_other_sources(mode):
                 assert_choices(g, want[j], f"{mode} {order} problem {j}")
 
 
-@pytest.mark.parametrize("levels,count,generated", [(8, 1 << 24, 1), (8, (1 << 24) - 1, 0), (7, 1 << 24, 0)])
-def test_generated_for_many_class_levels(levels, count, generated):
+@pytest.mark.parametrize("mode", ["level", "class", "objective"])
+@pytest.mark.parametrize("radix,count,generated", [
+    ([12] * 7 + [2, 1, 2], 1 << 24, 1), ([12] * 7 + [2, 1, 2], (1 << 24) - 1, 0), ([12] * 7 + [5, 1, 1], 1 << 24, 0),
+    ([3] * 14 + [8, 4, 4], 1 << 24, 1), ([3] * 14 + [3, 1, 43], 1 << 24, 0), ([12] * 7, 1 << 24, 0)])
+def test_generated_where_little_is_folded(radix, count, generated, mode):
     # the route at the edges of its rule, against the library's sweep (exact choices)
-    prob = wl.per_class(dataclasses.replace(problem(np.random.default_rng(8), [12] * 7, levels, True)), (1.0, 0.5))
+    prob = problem(np.random.default_rng(8), radix, 3, mode != "class")
+    item = (prob, wl.paper_objective(prob)) if mode == "objective" else prob
     src = [D.range_source(0, 12345, count)]
     got = []
     for jit in (1, 0):
-        with D.Plan(prob) as plan:
+        with D.Plan(item) as plan:
             plan.set_option(D.DY_OPT_JIT, jit)
             got.append([plan.select(src, stream=stream())[0] for _ in range(3)])
             assert plan.stats().generated_jobs == (generated if jit else 0)
