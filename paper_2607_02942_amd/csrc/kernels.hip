@@ -1853,7 +1853,8 @@ __global__ void __launch_bounds__(WG) k_score(const JobDev job, uint64_t unit_of
 // Per-plan scores of a RANGE source of 32-bit plan indices (uniform pressure
 // or the objective) by rows: a row fixes nodes 0..N-2 and its plans are node
 // y = N-1's implementations.  A wave takes `span` consecutive outputs (a
-// multiple of 64, from a multiple of it) that at most 64 rows cover.  Phase 1:
+// multiple of 64, from a multiple of it, or `lead` plans before one where a row
+// begins there) that at most 64 rows cover.  Phase 1:
 // each lane takes one row and forms its digits, prefix product (objective:
 // sums), demand sum and the longest paths into y and into the other sinks,
 // once for the row.  Phase 2: the wave scores the span, 64 consecutive plans at
@@ -1869,8 +1870,8 @@ __global__ void __launch_bounds__(WG) k_score(const JobDev job, uint64_t unit_of
 // Dynamic LDS: the recurrence column [N][WG] floats, the ids [N][WG], then the
 // (a, tau) and demand tables (N * R_max entries).
 template <bool OBJ>
-__global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t spans, uint32_t span, float* corr,
-                                                  float* cpo, float* dem, uint32_t* feas) {
+__global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t spans, uint32_t span, uint32_t lead,
+                                                  float* corr, float* cpo, float* dem, uint32_t* feas) {
     extern __shared__ float s_dyn[];
     __shared__ uint32_t s_cert[NBINS2], s_chk[NBINS2];
     __shared__ float4 s_pre[WG];  // per row: (prefix product or sum, demand sum, path into y, other sinks)
@@ -1928,7 +1929,8 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t spa
     for (uint64_t base = first; base < spans; base += stride) {
         __syncthreads();  // tables staged; the previous batch's rows consumed
         // phase 1: lane = row, from the row of the span's first plan
-        const uint64_t a0 = (base + (uint64_t)(tid >> 6)) * (uint64_t)span;  // the wave's first output
+        const uint64_t p0 = (base + (uint64_t)(tid >> 6)) * (uint64_t)span;  // `lead` plans before the wave's outputs
+        const uint64_t a0 = p0 > lead ? p0 - lead : 0;                       // its first output
         const uint64_t row0 = (J->begin + min(a0, count - 1)) / (uint64_t)ry;
         const uint64_t row = min(row0 + (uint64_t)lane, last_row);
         uint32_t x = (uint32_t)row;
@@ -1960,7 +1962,7 @@ __global__ void __launch_bounds__(WG) k_score_row(const JobDev job, uint64_t spa
         // phase 2: 64 consecutive plans per step
         if (a0 >= count) continue;
         const uint32_t qa = (uint32_t)(J->begin + a0 - row0 * (uint64_t)ry);  // the span's first plan within its rows
-        const uint32_t n = (uint32_t)min((uint64_t)span, count - a0);
+        const uint32_t n = (uint32_t)(min(p0 + span - lead, count) - a0);
         for (uint32_t s0 = 0; s0 < n; s0 += 64) {
             const uint32_t q = qa + min(s0 + (uint32_t)lane, n - 1);
             const uint32_t lr = mdiv(q, P->rmag[y]);  // local row
@@ -2465,19 +2467,24 @@ hipError_t launch_score(const JobDev& job, uint64_t units, float* corr, float* c
         // row, else as many times 64 as 64 rows cover from anywhere in the
         // first (every line of the outputs is then written by one store: 2^26
         // forkjoin8 plans from plan 12345 took 757 us in steps of 64 plans from
-        // a row's first, 538 us so)
-        uint32_t span = 64u * (uint32_t)ry;
-        if (job.begin % (uint64_t)ry != 0) span = 64u * std::max(1u, (62u * (uint32_t)ry + 1u) / 64u);
-        const uint64_t spans = (job.count + span - 1) / span;
+        // a row's first, 538 us so); rows of two plans, 65 of which such a span
+        // of 128 outputs would need, keep to the rows (2^24 plans at 8 levels
+        // 184 us, in spans of 64 outputs 230)
+        uint32_t span = 64u * (uint32_t)ry, lead = (uint32_t)(job.begin % (uint64_t)ry);
+        if (lead != 0 && ry > 2) {
+            span = 64u * ((62u * (uint32_t)ry + 1u) / 64u);
+            lead = 0;
+        }
+        const uint64_t spans = (job.count + lead + span - 1) / span;
         const uint64_t per = (uint64_t)(WG / 64) * SCORE_ROWS_PT;
         {
             const uint64_t gx = std::min<uint64_t>((spans + per - 1) / per, MAX_GRID_X);
             if (obj)
-                hipLaunchKernelGGL(k_score_row<true>, dim3((uint32_t)gx), dim3(WG), lds_row, s, job, spans, span, corr,
-                                   cp, dem, feas);
+                hipLaunchKernelGGL(k_score_row<true>, dim3((uint32_t)gx), dim3(WG), lds_row, s, job, spans, span, lead,
+                                   corr, cp, dem, feas);
             else
-                hipLaunchKernelGGL(k_score_row<false>, dim3((uint32_t)gx), dim3(WG), lds_row, s, job, spans, span, corr,
-                                   cp, dem, feas);
+                hipLaunchKernelGGL(k_score_row<false>, dim3((uint32_t)gx), dim3(WG), lds_row, s, job, spans, span, lead,
+                                   corr, cp, dem, feas);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

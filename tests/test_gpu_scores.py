@@ -32,7 +32,7 @@ def _gpu():
     yield
 
 
-@pytest.mark.parametrize("radix", [[5, 4, 1], [3, 5, 4, 7], [6, 7, 12], [2, 3, 255], [97]])
+@pytest.mark.parametrize("radix", [[5, 4, 1], [3, 5, 4, 7], [6, 7, 12], [2, 3, 255], [97], [9, 31, 2], [9, 31, 3]])
 @pytest.mark.parametrize("K", [1, 4, 5, 8])
 def test_range_scores_at_any_begin(radix, K):
     rng = np.random.default_rng([len(radix), K])
