@@ -22,6 +22,8 @@ from oracle import oracle as orc  # noqa: E402
 from paper_2607_02942_amd import dyplan as D  # noqa: E402
 from paper_2607_02942_amd import workload as wl  # noqa: E402
 
+from test_gpu_parity import assert_recovered  # noqa: E402
+
 pytestmark = pytest.mark.gpu
 RTOL = 1e-5
 
@@ -268,16 +270,15 @@ def test_all_plans_tie_overflow_then_exhaustive():
     assert all(c[0] == begin for c in got)
 
 
-def test_small_candidate_capacity_reseeds():
-    prob = wl.forkjoin8()
-    obj = wl.paper_objective(prob)
-    begin, count = 1000, 1 << 20
-    want = orc.obj_select_range(prob, obj, begin, count)
-    with D.Plan((prob, obj)) as plan:
-        plan.set_option(D.DY_OPT_CAND_CAPACITY, 16)
-        plan.set_option(D.DY_OPT_SAMPLE_STRIDE, 1 << 20)  # a poor seed: many candidates on the first pass
-        got = plan.select([D.range_source(0, begin, count)], stream=stream())[0]
-    assert_obj_choices(got, want, "reseed")
+@pytest.mark.parametrize("jit", [0, 2])
+def test_small_candidate_capacity_reseeds(jit):
+    # (a problem whose constructed seeds fall short of the best plan, as few do)
+    from test_gpu_range_sweep import problem
+    prob = problem(np.random.default_rng([173, 7]), [3] * 10, 2, True, edge_p=0.3)
+    obj = wl.paper_objective(prob, lambda_l=0.5, levels=(0.0, 0.3))
+    total = prob.n_plans()
+    assert_recovered((prob, obj), D.range_source(0, 0, total), orc.obj_select_range(prob, obj, 0, total),
+                     assert_obj_choices, jit)
 
 
 def test_force_fp64_matches():

@@ -525,16 +525,32 @@ def test_select_argument_errors():
                 plan.select([src], stream=stream())
 
 
-def test_overflow_recovered_by_reseeding():
+def assert_recovered(item, src, want, check, jit):
+    """`src` has more than 16 candidates at its first thresholds; a list of 16
+    overflows, and the sweep taken again on better seeds (not the exhaustive
+    path) chooses as `want`, by the library's sweep (jit 0) or after the
+    generated one (jit 2, on one sampled seed)."""
+    with D.Plan(item) as plan:
+        plan.set_option(D.DY_OPT_JIT, jit)
+        plan.set_option(D.DY_OPT_SAMPLE_STRIDE, 1 << 30)
+        plan.set_option(D.DY_OPT_CAND_CAPACITY, 1 << 24)
+        plan.select([src], stream=stream())
+        assert plan.stats().candidates > 16 and plan.stats().generated_jobs == (1 if jit else 0)
+        plan.set_option(D.DY_OPT_CAND_CAPACITY, 16)
+        for call in range(2):
+            got = plan.select([src], stream=stream())[0]
+            st = plan.stats()
+            assert st.fallbacks == 0 and st.candidates <= 16
+            check(got, want, f"reseeded, jit {jit}, call {call}")
+
+
+@pytest.mark.parametrize("jit", [0, 2])
+def test_overflow_recovered_by_reseeding(jit):
+    # factors within 1e-3 of each other: many plans about the best
     prob = wl.forkjoin8()
+    prob.p = (0.8 + 1e-3 * np.random.default_rng(31).random(prob.p.shape)).astype(np.float32)
     begin, count = 3000000, 2000000
-    with D.Plan(prob) as plan:
-        plan.set_option(D.DY_OPT_SAMPLE_STRIDE, 1 << 30)  # one seed sample: weak thresholds
-        plan.set_option(D.DY_OPT_CAND_CAPACITY, 1024)
-        got = plan.select([D.range_source(0, begin, count)], stream=stream())[0]
-        st = plan.stats()
-    assert_choices(got, orc.select_range(prob, begin, count), "reseeded")
-    assert st.fallbacks == 0
+    assert_recovered(prob, D.range_source(0, begin, count), orc.select_range(prob, begin, count), assert_choices, jit)
 
 
 @pytest.mark.parametrize("jit", [1, 0])

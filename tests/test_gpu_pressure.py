@@ -14,7 +14,8 @@ from oracle import oracle as orc  # noqa: E402
 from paper_2607_02942_amd import dyplan as D  # noqa: E402
 from paper_2607_02942_amd import workload as wl  # noqa: E402
 
-from test_gpu_parity import assert_choices, assert_scores, run_score, select, stream, tiny_problem  # noqa: E402
+from test_gpu_parity import (assert_choices, assert_recovered, assert_scores, run_score, select, stream,  # noqa: E402
+                             tiny_problem)
 
 pytestmark = pytest.mark.gpu
 
@@ -161,15 +162,11 @@ def test_generated_sweep_random_pressure():
                 assert_choices(got, want, f"trial {trial} ({n} nodes, radix <= {rmax}), call {call}")
 
 
-def test_small_capacity_reseeds_per_class():
+@pytest.mark.parametrize("jit", [0, 2])
+def test_small_capacity_reseeds_per_class(jit):
     prob = wl.per_class(wl.forkjoin8(), (1.0, 0.0))
-    begin, count = 4321, 1 << 20
-    want = orc.select_range(prob, begin, count)
-    with D.Plan(prob) as plan:
-        plan.set_option(D.DY_OPT_CAND_CAPACITY, 16)
-        plan.set_option(D.DY_OPT_SAMPLE_STRIDE, 1 << 20)
-        got = plan.select([D.range_source(0, begin, count)], stream=stream())[0]
-    assert_choices(got, want, "per class reseed")
+    begin, count = 123456, 1 << 21
+    assert_recovered(prob, D.range_source(0, begin, count), orc.select_range(prob, begin, count), assert_choices, jit)
 
 
 def test_score_per_class():
