@@ -1,5 +1,5 @@
 // Internal layout shared by the host side (host.cpp) and the kernels
-// (kernels.hip) of the plan scorer.  Not part of the public ABI.
+// (kernels.hip, solve.hip) of the plan scorer.  Not part of the public ABI.
 #pragma once
 
 #include <stdint.h>

@@ -435,7 +435,7 @@ struct dy_plan {
     bool stride_fixed = false;
     uint32_t cand_cap = 1u << 16;
     int force_fp64 = 0;
-    int use_climb = 1;                // local-search seeds: 0 never, 1 for calls of many sources, 2 always
+    int use_climb = 1;                // local-search seeds: 2 for every whole space of few nodes, else none
     std::vector<char> st_host;        // host copies of dy_plan_select_static's jobs and results
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     // A call that repeats the previous one (same job array, scratch clear) is
@@ -1802,7 +1802,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
                 J.hout = (dy_choice*)S.d_hres + (size_t)j * km;
                 J.hncand = (uint32_t*)(S.d_hres + S.res_ncand_off) + q;
                 J.hflags = (int32_t*)(S.d_hres + S.res_flags_off) + q;
-                if (n_src <= kDirectResults) J.hdone = S.d_done + q;
+                J.hdone = S.d_done + q;
             }
             J.fb_corr = S.fb_corr + (size_t)q * KMAX;
             J.fb_index = S.fb_index + (size_t)q * KMAX;

@@ -1551,7 +1551,8 @@ __global__ void __launch_bounds__(64) k_seed_cands(const JobDev* __restrict__ jo
 // Overflow recovery: the candidates gathered before the list overflowed
 // include certainly-feasible plans; fold their fp32 corr into the seeds (a
 // valid threshold comes from any certainly-feasible plan) and reset the list
-// for another scoring pass.  One wave per source; uniform pressure only.
+// for another scoring pass.  One wave per source.  (Under per-backend pressure
+// the range sweep's list keeps no CP; the seeds it leaves serve.)
 __global__ void __launch_bounds__(64) k_reseed(const JobDev* __restrict__ jobs) {
     JD J = cs(jobs + blockIdx.x);
     PD P = cs(J->prob);

@@ -799,7 +799,7 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
                     r0[q] = fminf(r0[q], div_threshold(t, c.x));
                 });
             else  // no such node
-                r0[0] = -INFINITY;
+                for (int q = 0; q < Q; ++q) r0[q] = -INFINITY;
         }
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -917,7 +917,8 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
         if (OBJ)
             lam = P->lam_l * (q == 0 ? 1.0f : q == 1 ? 0.5f : q == 2 ? 1.5f : 0.25f);
         else if (q == nl - 1)
-            lam = 1e30f;  // every node's fastest: the least CP, so a level without a seed has no plan
+            lam = 1e30f;  // about every node's fastest (ids within 2^-15 of it tie): a level of
+                          // few feasible plans may stay without a seed all the same (threshold -inf)
         else
             lam = P->lam0 * exp2f((MODE == SV_CLASS ? -13.0f : -7.0f) +
                                   (MODE == SV_CLASS ? 20.0f : 14.0f) * (float)q / (float)max(nl - 2, 1));
