@@ -1124,15 +1124,8 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
     // the source exhaustively; one workgroup certified 65,536 plans in 5 ms)
     const uint32_t total = s_nc, nc = total > J->cap ? 0u : total;
     if (nwg > 1 && tid < 32) J->wk[tid] = 0u;
-    // a list that overflowed: its seeds serve the next sweep of the source.  A
-    // source that was given seeds leaves every slot clear (a generated sweep,
-    // whose overflow this launch recovers, has sampled into all of them): the
-    // next call may give the job slot to another source without clearing it.
-    if (total > J->cap) {
-        if (tid < K) J->scert[tid * NSLOT] = s_seed[tid];
-    } else if (J->seeded) {
-        for (int i = tid; i < KMAX * NSLOT; i += WG) J->scert[i] = 0u;
-    }
+    // a list that overflowed: its seeds serve the next sweep of the source
+    if (tid < K && total > J->cap) J->scert[tid * NSLOT] = s_seed[tid];
 
     // certification: thresholds from the best seeds of all, then every
     // (candidate, level) that can still win is re-evaluated in fp64
@@ -1254,6 +1247,11 @@ __global__ void __launch_bounds__(WG, 5) k_solve(const JobDev* __restrict__ jobs
         J->out[tid] = c;
         s_out[tid] = c;
     }
+    // A source that was given seeds leaves every slot clear (a generated sweep,
+    // whose overflow this launch recovers, has sampled into all of them): the
+    // next call may give the job slot to another source without clearing it.
+    if (J->seeded && total <= J->cap)
+        for (int i = tid; i < KMAX * NSLOT; i += WG) J->scert[i] = 0u;
     const int32_t flags = total > J->cap ? (int32_t)JF_OVERFLOW : 0;
     if (tid == 0) {
         *J->ncand = total;
