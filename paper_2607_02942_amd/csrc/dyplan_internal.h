@@ -209,6 +209,7 @@ struct JobDev {
     int32_t nwg;
     int32_t seeded;
     int32_t whole;            // the range is the whole plan space
+    int32_t reseed;           // after an overflow: the listed candidates raise the seeds (else the sweep's own are there)
 };
 
 

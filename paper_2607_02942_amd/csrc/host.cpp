@@ -2074,6 +2074,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
                 const int tries = grp[j] == G_SOLVE || grp[j] == G_SOLVE + 2 ? 1 : kReseedRounds;
                 if (round < tries) {
                     J.seeded = 1;
+                    J.reseed = grp[j] < kSweepGroups ? round == 0 : grp[j] < G_SOLVE;
                     ++rp.n[g];
                     if (g < G_JIT) rp.units[g] = std::max(rp.units[g], J.units);
                     if (g >= G_SOLVE) add_solve(rp, g - G_SOLVE, J, h->hdesc[src[j].problem]);

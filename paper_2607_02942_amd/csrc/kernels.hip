@@ -1551,13 +1551,14 @@ __global__ void __launch_bounds__(64) k_seed_cands(const JobDev* __restrict__ jo
 // Overflow recovery: the candidates gathered before the list overflowed
 // include certainly-feasible plans; fold their fp32 corr into the seeds (a
 // valid threshold comes from any certainly-feasible plan) and reset the list
-// for another scoring pass.  One wave per source.  (Under per-backend pressure
-// the range sweep's list keeps no CP; the seeds it leaves serve.)
+// for another scoring pass.  One wave per source.  (Lists of the range sweep,
+// which leaves its own seeds, are not read: a wave took 4 ms over 65,536
+// candidates at 32 levels.)
 __global__ void __launch_bounds__(64) k_reseed(const JobDev* __restrict__ jobs) {
     JD J = cs(jobs + blockIdx.x);
     PD P = cs(J->prob);
     const int lane = threadIdx.x;
-    const uint32_t nc = min(*J->ncand, J->cap);
+    const uint32_t nc = J->reseed ? min(*J->ncand, J->cap) : 0u;
     for (int k = 0; k < P->k; ++k) {
         uint32_t e;
         if (P->obj) {  // every candidate is admissible: its fp32 estimate of J_k
