@@ -488,13 +488,15 @@ __device__ __forceinline__ void pair_eval(PD P, const uint8_t* ids, double* f, i
 // thresholds (every workgroup of a source the same) and building the tables.
 // The workgroup that ends last certifies the candidates in fp64 and writes
 // the choices.
-// Bound by chains of dependent LDS reads (seeding, the three folds, the
-// 64-bit recurrences), not by memory or arithmetic: a call of one small source
-// is mostly those chains, one after the other.  us a pass, the separate
-// sampling, table, plan-by-plan sweep and certification launches -> this one:
-// 4,096 six-node requests 1,196-1,405 -> 226, their objective 1,111 -> 161,
-// 512 mixed 416 -> 110, 1,000 under per-backend pressure 545 -> 251, one
-// fork-join of 4.3e8 plans 87 -> 44, one layered space of 4.3e9 611 -> 62.
+// Bound by latency: a workgroup is one serial chain (seeding, three folds,
+// heads, unfolding, the 64-bit recurrences) of dependent reads.  Per CU and
+// cycle it issues 0.36 vector instructions on 4,096 six-node requests (1 is the
+// rate of the four SIMDs), 0.10 and 0.18 on single ranges of 4.3e8 and 4.3e9
+// plans, and 0.05, 0.01 and 0.02 LDS instructions; HBM is idle.  us a pass, the
+// separate sampling, table, plan-by-plan sweep and certification launches and
+// this one, timed in turn: 4,096 six-node requests 1,563 / 211, their objective
+// 1,106 / 163, 512 mixed 432 / 116, 1,000 under per-backend pressure 501 / 154,
+// one fork-join of 4.3e8 plans 111 / 42, one layered space of 4.3e9 717 / 56.
 // Five waves per SIMD: with one more register group the batches, whose
 // workgroups wait on LDS chains most of the time, ran 9 % longer; at six (80
 // registers, spills) small sources run 3 to 10 % longer.
