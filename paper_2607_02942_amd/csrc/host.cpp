@@ -93,7 +93,7 @@ struct HostProb {
 
 struct Scratch {
     size_t jobs = 0;            // sources the buffers hold
-    bool clean = false;         // every job slot's seeds, counters and flags are zero (no k_init needed)
+    size_t clean = 0;           // so many leading job slots' seeds, counters and flags are zero (no k_init needed)
     uint32_t* sync = nullptr;   // [jobs] certification block counters
     uint32_t* wk = nullptr;     // [jobs][SOLVE_WK] counters of the RANGE sources' workgroups
     uint32_t cap = 0;           // candidate slots per source
@@ -535,7 +535,7 @@ size_t layout_scratch(Scratch& s, char* d, size_t njobs, uint32_t cap, int km) {
     s.fb_corr = (uint64_t*)(d + o_fbc);
     s.fb_index = (uint64_t*)(d + o_fbi);
     s.cand = (Cand*)(d + o_cand);
-    s.clean = false;  // the next call clears the scratch first
+    s.clean = 0;  // the next call clears the scratch first
     return off;
 }
 
@@ -1970,7 +1970,8 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         for (int q = 0; q < n_src; ++q) __atomic_store_n(S.h_done + q, 0u, __ATOMIC_RELAXED);
     bool exhausted = h->force_fp64 != 0;
     bool launched = false;
-    if (!stat && h->use_graph && !h->timing && !h->force_fp64 && S.clean && !changed) {
+    const size_t clean = S.clean;  // (a smaller call leaves the slots past its sources as they are)
+    if (!stat && h->use_graph && !h->timing && !h->force_fp64 && clean >= (size_t)n_src && !changed) {
         if (!h->graph) {  // capture once; a failure falls back to direct launches for this plan
             h->graph = capture_graph(h, [&](hipStream_t st, const Check& ck) {
                 issue_pre(st, ck);
@@ -1980,7 +1981,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
             if (!h->graph) h->use_graph = 0;
         }
         if (h->graph) {
-            S.clean = false;
+            S.clean = 0;
             chk(hipGraphLaunch(h->graph, s), "hipGraphLaunch");
             launched = true;
         }
@@ -1990,10 +1991,10 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         // A call that ends with every source certified and no flag raised leaves
         // the scratch clear (the certification's last blocks re-zero the seeds);
         // anything else, or a fresh allocation, clears it here.
-        if (!S.clean || h->force_fp64)
+        if (clean < (size_t)n_src || h->force_fp64)
             for (int c = 0; c < n_src; c += 65535)
                 chk(launch_init(S.d_jobs + c, std::min(65535, n_src - c), s), "init");
-        S.clean = false;
+        S.clean = 0;
         if (!h->force_fp64) {
             issue_pre(s, chk);
             issue_mid(s, chk);
@@ -2138,7 +2139,7 @@ static int select_impl(dy_plan* h, const dy_source* src, int32_t n_src, dy_choic
         flagged = false;
         for (int q = 0; q < n_src; ++q) flagged = flagged || S.h_flags[q] != 0;
     }
-    S.clean = !exhausted && !flagged;
+    S.clean = exhausted || flagged ? 0 : std::max(clean, (size_t)n_src);
     h->stats = stats;
     return DY_OK;
 }

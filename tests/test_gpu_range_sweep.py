@@ -408,3 +408,34 @@ def test_overflows_of_every_kind_in_one_call():
                 assert plan.stats().fallbacks == 6  # two sources of three levels
                 for g, w in zip(got, want):
                     assert_choices(g, w, f"jit {jit} call {call}")
+
+
+def test_smaller_call_between_an_overflow_and_a_larger_call():
+    # the eighth source of a call ends exhaustively; a call of two sources comes
+    # between it and others of eight, whose last job slot must not see what it left
+    rng = np.random.default_rng(88)
+    low = problem(rng, [6, 5, 7, 4, 6], 3, True)
+    low = dataclasses.replace(low, p=low.p * np.float32(0.1), slo=1e6)
+    tied = [dataclasses.replace(low, p=np.full_like(low.p, p), tau=np.ones_like(low.tau)) for p in (0.9, 0.1)]
+    probs, total = [low] + tied, low.n_plans()
+    want = [orc.select_range(p, 0, total) for p in probs]
+    rows = np.stack([rng.integers(0, r, 5000) for r in low.radix], axis=1).astype(np.uint8)
+    want_rows = orc.select_rows(low, rows)
+    d = torch.from_numpy(rows).cuda()
+    with D.Plan(probs) as plan:
+        plan.set_option(D.DY_OPT_JIT, 0)
+        plan.set_option(D.DY_OPT_CAND_CAPACITY, 16)
+
+        def ranges(js):
+            got = plan.select([D.range_source(j, 0, total) for j in js], stream=stream())
+            for g, j in zip(got, js):
+                assert_choices(g, want[j], f"{js} problem {j}")
+        for last in ("rows", "tied"):
+            ranges([0] * 7 + [1])
+            assert plan.stats().fallbacks == 3
+            ranges([0, 0])
+            if last == "tied":
+                ranges([0] * 7 + [2])
+            else:
+                for g in plan.select([D.rows_source(0, d, 5000, 5)] * 8, stream=stream()):
+                    assert_choices(g, want_rows, "rows")
