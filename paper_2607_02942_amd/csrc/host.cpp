@@ -1607,7 +1607,9 @@ void split_source(JobDev& J, const ProbDev& D, uint64_t share) {
         seed_boxes(J, D);
     const uint64_t several = (J.units + WG * kSolveSteps - 1) / (WG * kSolveSteps), one = (J.units + WG - 1) / WG;
     uint64_t n = several;
-    if (4 * n <= 3 * (share / kSolveWgs)) {
+    // (a source that fits one workgroup keeps to it: 27 requests of 1.5e4 plans 35 us,
+    // in several workgroups each, with their hand-over, 41)
+    if (n > 1 && 4 * n <= 3 * (share / kSolveWgs)) {
         // a workgroup takes every n-th head, so factors that n has in common with
         // the radices give it heads of the same ids, and one workgroup most of
         // those that pass (315 candidates of forkjoin8: 256 workgroups 54 us, 253
