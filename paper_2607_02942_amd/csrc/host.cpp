@@ -1613,9 +1613,9 @@ void split_source(JobDev& J, const ProbDev& D, uint64_t share) {
         // a workgroup takes every n-th head, so factors that n has in common with
         // the radices give it heads of the same ids, and one workgroup most of
         // those that pass (315 candidates of forkjoin8: 256 workgroups 54 us, 253
-        // or 243 45)
+        // or 243 45); fewer than asked for would take a step more
         n = std::min(one, share / kSolveWgs);
-        while (n > 16 && (n % 2 == 0 || n % 3 == 0)) n += n >= one ? 1 : -1;
+        while (n > 16 && (n % 2 == 0 || n % 3 == 0)) ++n;
     }
     J.nwg = (int32_t)std::min(std::max<uint64_t>(share, 1), n);
 }
